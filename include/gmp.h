@@ -69,8 +69,12 @@ typedef enum {
  *                         accumulation as an FP32 (hi, lo) pair updated with
  *                         an error-free two-sum; cross-lane reduction, the
  *                         moment-to-component map and the norm in FP64.
- *  GMP_FP32_WIDE:         exponentials and radial sums in FP32; monomials of
- *                         the FP64 displacement and the per-lane accumulation
+ *                         gmp_features without components, whose results are
+ *                         FP32 alone, computes them as GMP_FP32_WIDE does
+ *                         (faster and at least as accurate; the two agree to
+ *                         FP32 rounding).
+ *  GMP_FP32_WIDE:         exponentials and radial sums in FP32; solid harmonics
+ *                         of the FP64 displacement and the per-lane accumulation
  *                         in FP64 (one FP64 fma per term: on gfx950 FP64 FMA
  *                         issues at the non-packed FP32 rate, so widening is
  *                         cheaper than a two-sum and loses nothing).

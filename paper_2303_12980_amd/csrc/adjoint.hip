@@ -32,8 +32,6 @@ template <> struct Real<true> { using T = double; };
 
 __device__ inline float exp_scaled(float a, float q) { return __builtin_amdgcn_exp2f(a * q); }
 __device__ inline double exp_scaled(double a, double q) { return exp(a * q); }
-__device__ inline float fma_(float a, float b, float c) { return fmaf(a, b, c); }
-__device__ inline double fma_(double a, double b, double c) { return fma(a, b, c); }
 
 
 // One wavefront per index: centres get their coefficients, every index

@@ -25,7 +25,7 @@ void launch_reverse(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, con
 int64_t max_chunks(const gmp_plan *p, int64_t n_atoms, int64_t pairs);
 void launch_overlap(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, double *partial, int64_t *nch,
                     int64_t *chunk_off, int64_t *scan_aux, unsigned long long *counter, double4 *rw4,
-                    int32_t *astruct, int64_t pairs_bound, hipStream_t s);
+                    int32_t *astruct, int64_t pairs_bound, bool components, hipStream_t s);
 void launch_finish(const gmp_plan *p, int64_t N, const double *partial, const int64_t *chunk_off,
                    const int32_t *order, void *features,
                    double *components, hipStream_t s);
@@ -444,17 +444,25 @@ gmp_status gmp_plan_create(const gmp_probe_desc *d, gmp_precision precision, gmp
     P.rank_lt[s] = r;
   }
   // moment -> component maps and weights
-  std::vector<double> T;
+  std::vector<double> T, H;
   for (int l = 0; l <= kMaxL; ++l) {
     P.toff[l] = (int)T.size();
+    P.hoff[l] = (int)H.size();
     std::vector<double> Tl = harmonic_matrix(l);
     T.insert(T.end(), Tl.begin(), Tl.end());
+    // from the moments of the solid harmonics: the columns of the monomials
+    // with z exponent 0 or 1, in the harmonics' order
+    for (int row = 0; row < ncomp(l); ++row)
+      for (int c = 0; c <= 1; ++c)
+        for (int a = l - c; a >= 0; --a) H.push_back(Tl[(size_t)row * ncomp(l) + midx(l, a, l - a - c)]);
     for (int a = l; a >= 0; --a)
       for (int b = l - a; b >= 0; --b) {
         const int c = l - a - b;
         P.weight[doff(l) + midx(l, a, b)] = fact(l) / (fact(a) * fact(b) * fact(c));
       }
   }
+  const size_t hbase = T.size();
+  T.insert(T.end(), H.begin(), H.end());
   std::vector<int> kc(p->E);
   for (int e = 0; e < p->E; ++e) kc[e] = d->prim_offsets[e + 1] - d->prim_offsets[e];
   // tabulated radial factors: per (slot, element) and interval [r_k, r_k+1]
@@ -529,6 +537,7 @@ gmp_status gmp_plan_create(const gmp_probe_desc *d, gmp_precision precision, gmp
   P.coef32 = (const float *)base;
   P.coef64 = (const double *)(base + o64);
   P.T = (const double *)(base + oT);
+  P.H = P.T + hbase;
   P.kcount = (const int *)(base + ok);
   P.rtab = brt > 0 ? (const float4 *)(base + ort) : nullptr;
   p->tuning.chunk_pairs = 2048;
@@ -851,7 +860,8 @@ gmp_status gmp_features(const gmp_plan *p, const gmp_batch *b, const gmp_neighbo
   BatchDev bt = to_dev(b);
   NbrDev nb = to_dev(n);
   const int64_t pairs = n->n_pairs > 0 && n->n_pairs <= n->capacity ? n->n_pairs : n->capacity;
-  launch_overlap(p, bt, nb, L.partial, L.nch, L.chunk_off, L.scan_aux, L.counter, L.rw4, L.astruct, pairs, s);
+  launch_overlap(p, bt, nb, L.partial, L.nch, L.chunk_off, L.scan_aux, L.counter, L.rw4, L.astruct, pairs,
+                 components != nullptr, s);
   launch_finish(p, N, L.partial, L.chunk_off, n->order, features, components, s);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_error(e, "feature kernels");
@@ -888,7 +898,8 @@ gmp_status gmp_features_noalloc(const gmp_plan *p, const gmp_batch *b, const gmp
     return set_error(GMP_E_NOMEM, "gmp_features_noalloc needs " + std::to_string(c.off) +
                                       " bytes of scratch; its fixed array holds " + std::to_string(cap));
   hipStream_t s = (hipStream_t)stream;
-  launch_overlap(p, to_dev(b), to_dev(n), partial, nch, chunk_off, scan_aux, counter, rw4, astruct, pairs, s);
+  launch_overlap(p, to_dev(b), to_dev(n), partial, nch, chunk_off, scan_aux, counter, rw4, astruct, pairs,
+                 components != nullptr, s);
   launch_finish(p, N, partial, chunk_off, n->order, features, components, s);
   e = hipGetLastError();
   if (e != hipSuccess) return hip_error(e, "feature kernels");

@@ -11,6 +11,7 @@
 #include <stdint.h>
 
 #include <string>
+#include <type_traits>
 
 #include "../../include/gmp.h"
 
@@ -69,6 +70,17 @@ __host__ __device__ constexpr MonoTable make_mono_table() {
   return t;
 }
 
+// Solid harmonics.  A harmonic polynomial of degree l is determined by its
+// coefficients of the 2l+1 monomials x^a y^b z^c with c = 0 or 1 (Laplace's
+// equation gives the rest), so the harmonic polynomials Y_k whose c <= 1 part
+// is one such monomial are a basis: P = sum_k p_k Y_k with p_k the
+// coefficient of monomial k in P.  The moments of Y_k (25 up to degree 4,
+// where the monomials are 35) carry all that the components P_abc need.
+// Order inside degree l: c = 0 with a = l..0, then c = 1 with a = l-1..0.
+__host__ __device__ constexpr int nharm(int lmax) { return (lmax + 1) * (lmax + 1); }
+// degree of harmonic m
+__host__ __device__ constexpr int hdeg(int m) { return m < 1 ? 0 : (m < 4 ? 1 : (m < 9 ? 2 : (m < 16 ? 3 : 4))); }
+
 // Adjoint coefficient block per (centre, slot): the monomial coefficients M
 // [nmono(L)] of the upstream-weighted polynomial, padded to a multiple of 4
 // entries so the pair kernels' wavefront-uniform LDS reads can be 16-byte
@@ -81,6 +93,13 @@ __host__ __device__ constexpr int tmat_size() {
   return n;
 }
 constexpr int kTmat = tmat_size();
+// entries of the moment -> component maps over solid harmonics (ncomp(l) rows of 2l+1)
+__host__ __device__ constexpr int hmat_size() {
+  int n = 0;
+  for (int l = 0; l <= kMaxL; ++l) n += ncomp(l) * (2 * l + 1);
+  return n;
+}
+constexpr int kHmat = hmat_size();
 __host__ __device__ constexpr int round4(int n) { return (n + 3) & ~3; }
 __host__ __device__ constexpr int coef_m(int lmax) { return round4(nmono(lmax)); }
 __host__ __device__ constexpr int coef_block(int lmax) { return coef_m(lmax); }
@@ -119,6 +138,8 @@ struct PlanDev {
   const int *kcount;              // [E]
   const double *T;                // moment->component maps, per order l: ncomp(l)^2 at toff[l]
   int toff[kMaxL + 1];
+  const double *H;                // moment->component maps over solid harmonics, per order l: ncomp(l) rows of 2l+1
+  int hoff[kMaxL + 1];
   double weight[35];              // l!/(a!b!c!) by global monomial index (same (a,b,c) ordering)
 };
 
@@ -231,6 +252,45 @@ __device__ inline void image_shift(const Cell9 &c, int n1, int n2, int n3, doubl
   image_shift(c.a, n1, n2, n3, sx, sy, sz);
 }
 
+__device__ inline float fma_(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ inline double fma_(double a, double b, double c) { return fma(a, b, c); }
+
+// The solid harmonics Y_m of degree <= LMAX at (x, y, z), in order: calls
+// f(m, Y_m) with m a compile-time constant (32 operations for the 25 of degree
+// <= 4).  With BARRIER the compiler keeps the degrees apart: only the products
+// the next degrees share stay live.
+template <int M> using Idx = std::integral_constant<int, M>;
+template <int LMAX, bool BARRIER, typename T, typename F>
+__device__ inline void for_harmonics(T x, T y, T z, F &&f) {
+  auto fence = [] { if constexpr (BARRIER) __builtin_amdgcn_sched_barrier(0); };
+  f(Idx<0>{}, (T)1);
+  if constexpr (LMAX >= 1) { f(Idx<1>{}, x); f(Idx<2>{}, y); f(Idx<3>{}, z); }
+  if constexpr (LMAX >= 2) {
+    fence();
+    const T X = x * x, W = y * y, Z = z * z, xy = x * y, xz = x * z, yz = y * z;
+    const T u = X - Z, v = W - Z;
+    f(Idx<4>{}, u); f(Idx<5>{}, xy); f(Idx<6>{}, v); f(Idx<7>{}, xz); f(Idx<8>{}, yz);
+    if constexpr (LMAX >= 3) {
+      fence();
+      const T third = (T)(1.0 / 3.0);
+      const T a = fma_((T)-3, Z, X), b = fma_((T)-3, Z, W);
+      const T c = fma_(-third, Z, X), d = fma_(-third, Z, W);
+      f(Idx<9>{}, x * a); f(Idx<10>{}, y * u); f(Idx<11>{}, x * v); f(Idx<12>{}, y * b);
+      f(Idx<13>{}, z * c); f(Idx<14>{}, xy * z); f(Idx<15>{}, z * d);
+      if constexpr (LMAX >= 4) {
+        fence();
+        const T ZZ = Z * Z;
+        f(Idx<16>{}, fma_(X, fma_((T)-6, Z, X), ZZ));
+        f(Idx<17>{}, xy * a);
+        f(Idx<18>{}, fma_(u, v, (T)(-2.0 / 3.0) * ZZ));
+        f(Idx<19>{}, xy * b);
+        f(Idx<20>{}, fma_(W, fma_((T)-6, Z, W), ZZ));
+        f(Idx<21>{}, xz * u); f(Idx<22>{}, yz * c); f(Idx<23>{}, xz * d); f(Idx<24>{}, yz * v);
+      }
+    }
+  }
+}
+
 // Structure of index g (atom or reference point).
 __device__ inline int struct_of_index(const BatchDev &bt, int64_t g) {
   return g < bt.n_atoms ? struct_of_atom(bt.atom_offsets, bt.n_structs, g)
@@ -315,7 +375,7 @@ struct WsLayout {
   int32_t *long_q;        // [N] slots whose lists the long-list fill kernel writes
   int32_t *sid_tmp;       // [N] atoms placed in their bins in arrival order (before the in-bin ordering)
   int64_t *scan_aux;      // scan block sums
-  double *partial;        // overlap partial moments [chunk][sigma][monomial]
+  double *partial;        // overlap partial moments [chunk][slot][harmonic]
   int64_t *nch;           // [N] chunks per centre
   int64_t *chunk_off;     // [N+1] first chunk of each centre
   unsigned long long *counter;  // work-item counter of the persistent kernels

@@ -22,8 +22,6 @@ constexpr MonoTable kMT = make_mono_table();
 
 __device__ inline float exp_scaled(float a, float q) { return __builtin_amdgcn_exp2f(a * q); }
 __device__ inline double exp_scaled(double a, double q) { return exp(a * q); }
-__device__ inline float fma_(float a, float b, float c) { return fmaf(a, b, c); }
-__device__ inline double fma_(double a, double b, double c) { return fma(a, b, c); }
 
 // Persistent: wavefronts pull (centre, chunk) items; lanes take consecutive
 // pairs; the centre's coefficients are staged in LDS per item.

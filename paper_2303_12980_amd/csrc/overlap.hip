@@ -5,30 +5,34 @@
 // defines the probe as an MCSH angular probe times a Gaussian radial probe
 // and the density as per-element Gaussian primitives):
 //   mu_{i,l,s,abc} += c_{l,s,e_j}(q) P_abc(d),
-//   c_{l,s,e}(q) = sum_k A_{l,s,e,k} exp(-gamma_{s,e,k} q),
-// each pair term scaled by the neighbour's occupancy (disordered structures;
-// 1 when none is given), which rides in the fourth component of its packed
-// wrapped position and multiplies the monomial recursion's seed.
-// P_abc is a homogeneous polynomial of degree l, so the kernel accumulates
-// the Cartesian moments  M_{i,s,m} = sum_j c_{deg m,s,e_j}(q_j) x^a y^b z^c
-// of every monomial m of each requested degree, and the norm kernel maps
-// moments to components with the plan's exact integer matrices (FP64).
+//   c_{l,s,e}(q) = sum_k A_{l,s,e,k} exp(-gamma_{s,e,k} q).
+// P_abc is a harmonic polynomial of degree l, so the kernel accumulates the
+// moments  M_{i,s,k} = sum_j c_{deg k,s,e_j}(q_j) Y_k(d_j)  of a basis of 2l+1
+// solid harmonics per degree (or, below, of every monomial of each degree),
+// and the norm kernel maps moments to components with the plan's exact integer
+// matrices (FP64).  Each pair term is scaled by the neighbour's occupancy
+// (disordered structures), which rides in the fourth component of its packed
+// wrapped position.
 //
 // Work decomposition: persistent wavefronts pull work items (a chunk of one
 // centre's list) from a global counter; lanes take consecutive pairs.  The
-// list is ordered by cutoff shell first, so the pairs a sigma uses form a
-// prefix and each sigma is one pass over its own prefix, without testing q.
-// Lanes read the coefficient row of their own neighbour's species from the
-// LDS copy of the plan table.  The local density of order -1 is one more
-// cutoff slot whose pass accumulates only the degree-0 moment
-// rho = sum_j sum_k B exp(-beta q).
+// list is ordered by cutoff shell first, so the pairs a slot uses form a
+// prefix.  Lanes read the coefficient row of their own neighbour's species
+// from the LDS copy of the plan table.  The local density of order -1 is one
+// more cutoff slot, of whose moments only the degree-0 one
+// rho = sum_j sum_k B exp(-beta q) is read back.
 //
-// Precision policies (template MODE):
-//   FP32 compensated: displacement rounded to FP32; monomials, exp2, radial
-//              sums and products in FP32; per-lane accumulation as FP32
-//              (hi, lo) two-sum pairs; cross-lane reduction in FP64.
-//   FP32 wide: FP32 exp2 and radial sums, FP64 monomials and accumulation.
-//   FP64:      everything FP64 (exp in FP64), plain accumulation.
+// Arithmetic (template MODE):
+//   ACC_F64:   everything FP64 (exp in FP64), harmonics.
+//   ACC_WIDE:  FP32 exponentials and radial sums; FP64 harmonics and
+//              accumulation (one FP64 fma per term, which issues at the
+//              non-packed FP32 rate on gfx950).  FP32-wide plans, and
+//              FP32-compensated ones where only the FP32 features are asked for.
+//   ACC_TERMS: FP32 pair terms throughout (displacement, monomials,
+//              exponentials, radial sums, products); per-lane accumulation as
+//              FP32 (hi, lo) error-free sums.  FP32-compensated plans where
+//              the FP64 components are asked for.
+// Cross-lane reduction, moment -> component map and norm are FP64 throughout.
 #include <map>
 #include <mutex>
 #include <type_traits>
@@ -40,23 +44,22 @@ namespace {
 
 constexpr MonoTable kMT = make_mono_table();
 
+enum AccMode { ACC_F64 = 0, ACC_WIDE = 1, ACC_TERMS = 2 };
+// accumulated moments per slot
+__host__ __device__ constexpr int n_moments(int mode, int lmax) { return mode == ACC_TERMS ? nmono(lmax) : nharm(lmax); }
+
 __device__ inline float exp_scaled(float a, float q) { return __builtin_amdgcn_exp2f(a * q); }
 __device__ inline double exp_scaled(double a, double q) { return exp(a * q); }
-__device__ inline float fma_(float a, float b, float c) { return fmaf(a, b, c); }
-__device__ inline double fma_(double a, double b, double c) { return fma(a, b, c); }
 
-// Chunks of one centre's list: fixed-size pieces of kc pairs (kc = 0: whole
-// list), so the decomposition of a centre depends on its own list only and
-// a batched launch sums in the same order as a launch over one structure.
-// Per list slot: the number of work items of its list (fixed-size pieces
-// of kc pairs, kc = 0: whole list, each split into ng groups of cutoff
-// slots, so the decomposition of a centre depends on its own list only and
-// a batched launch sums in the same order as a launch over one structure),
-// its structure, and its wrapped position as an AoS double4 (one 32-byte
-// gather per neighbour).  The first thread also clears the work-item counter.
+// Per list slot: the number of chunks of its list (fixed-size pieces of kc
+// pairs, kc = 0: whole list, so the decomposition of a centre depends on its
+// own list only and a batched launch sums in the same order as a launch over
+// one structure), its structure, and its wrapped position as an AoS double4
+// (one 32-byte gather per neighbour).  The first thread also clears the
+// work-item counter.
 // Indices g < n_total get their structure and packed position; centres
 // c < n_centres their chunk count.
-__global__ void k_overlap_prep(BatchDev bt, NbrDev nb, int kc, int ng, int64_t *nch, double4 *rw4,
+__global__ void k_overlap_prep(BatchDev bt, NbrDev nb, int kc, int64_t *nch, double4 *rw4,
                                int32_t *astruct, unsigned long long *counter) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i == 0) *counter = 0ull;
@@ -64,7 +67,7 @@ __global__ void k_overlap_prep(BatchDev bt, NbrDev nb, int kc, int ng, int64_t *
     const int64_t cnt = nb.offsets[i + 1] - nb.offsets[i];
     // a list that ends past the capacity was not written (overflowed no-sync
     // build, reported in the status word): no work items, zero moments
-    nch[i] = nb.offsets[i + 1] > nb.capacity ? 0 : ng * (kc > 0 ? (cnt > kc ? (cnt + kc - 1) / kc : 1) : 1);
+    nch[i] = nb.offsets[i + 1] > nb.capacity ? 0 : (kc > 0 && cnt > kc ? (cnt + kc - 1) / kc : 1);
   }
   if (i < n_total(bt)) {
     const int st = struct_of_index(bt, i);
@@ -73,7 +76,15 @@ __global__ void k_overlap_prep(BatchDev bt, NbrDev nb, int kc, int ng, int64_t *
   }
 }
 
+// List slot of chunk q.  Chunk q belongs to slot q itself where every list
+// before it is one chunk (the common case: one round trip in place of the
+// bisection's dozen dependent ones); otherwise to an earlier slot, or a later
+// one where lists before it were not written.
 __device__ inline int64_t centre_of_chunk(const int64_t *chunk_off, int64_t N, int64_t q) {
+  if (q < N) {
+    const int64_t a = uniform64(chunk_off[q]), b = uniform64(chunk_off[q + 1]);
+    if (a == q && b == q + 1) return q;
+  }
   int64_t lo = 0, hi = N;  // chunk_off[lo] <= q < chunk_off[lo+1]
   while (hi - lo > 1) {
     const int64_t mid = (lo + hi) >> 1;
@@ -82,11 +93,15 @@ __device__ inline int64_t centre_of_chunk(const int64_t *chunk_off, int64_t N, i
   return lo;
 }
 
-// Accumulation policies of the overlap kernel.
-enum AccMode { ACC_F64 = 0, ACC_TWOSUM = 1, ACC_WIDE = 2 };
-
-// Per-lane accumulator of one sigma's moments.
-template <int MODE, int NM> struct Acc;
+// Per-lane accumulators of one slot's moments.
+template <int MODE, int NM> struct Acc {
+  double v[NM];
+  __device__ void zero() {
+#pragma unroll
+    for (int m = 0; m < NM; ++m) v[m] = 0.0;
+  }
+  __device__ double value(int m) const { return v[m]; }
+};
 // FP32 (hi, lo) pairs updated with an error-free sum: Dekker's Fast2Sum
 // on the two addends ordered by magnitude (exact when the first is the
 // larger).  It yields the same exact rounding error, hence the same (hi,
@@ -94,7 +109,7 @@ template <int MODE, int NM> struct Acc;
 // magnitudes, two selects, three additions), but reads the old sum only
 // before the new one is formed, so the new sum takes its register without a
 // copy back.
-template <int NM> struct Acc<ACC_TWOSUM, NM> {
+template <int NM> struct Acc<ACC_TERMS, NM> {
   float hi[NM], lo[NM];
   __device__ void zero() {
 #pragma unroll
@@ -109,58 +124,73 @@ template <int NM> struct Acc<ACC_TWOSUM, NM> {
   }
   __device__ double value(int m) const { return (double)hi[m] + (double)lo[m]; }
 };
-// FP64 accumulators (FP64 path and the wide FP32 path).
-template <int NM> struct Acc<ACC_F64, NM> {
-  double v[NM];
-  __device__ void zero() {
-#pragma unroll
-    for (int m = 0; m < NM; ++m) v[m] = 0.0;
-  }
-  __device__ double value(int m) const { return v[m]; }
-};
-template <int NM> struct Acc<ACC_WIDE, NM> : Acc<ACC_F64, NM> {};
 
-// Fixed-order cross-lane sum of NV per-lane doubles, written to dst[0..NV):
-// rounds of 8 columns are transposed through LDS (each lane sums 8 rows of
-// one column), then the 8 row-group partials are combined with xor shuffles.
-// Every lane of a column group computes the same bits; lanes 0..7 store.
-template <int NV>
-__device__ inline void wave_reduce_store(const double (&v)[NV], double *dst, double *lds) {
-  const int lane = lane_id();
-  const int col = lane & 7, grp = lane >> 3;
-#pragma unroll
-  for (int base = 0; base < NV; base += 8) {
-#pragma unroll
-    for (int c = 0; c < 8; ++c)
-      if (base + c < NV) lds[lane * 9 + c] = v[base + c];
-    wave_lds_sync();
-    double s = 0.0;
-    if (base + col < NV) {
-#pragma unroll
-      for (int r = 0; r < 8; ++r) s += lds[(grp * 8 + r) * 9 + col];
-    }
-    s += __shfl_xor(s, 8, kWave);
-    s += __shfl_xor(s, 16, kWave);
-    s += __shfl_xor(s, 32, kWave);
-    if (lane < 8 && base + lane < NV) dst[base + lane] = s;
-    wave_lds_sync();
-  }
+// Slots of one pass: several cutoff slots, consecutive in cutoff order, share
+// a walk over the list, and with it the displacement, the harmonics (or
+// monomials) and the loads of every pair.  Their accumulators bound how many
+// fit.  Harmonics, l = 4: two slots' 2 x 25 doubles leave two wavefronts per
+// SIMD (held to three they spill: 0.25 instead of 0.23 ms on 4096 atoms).
+// FP32 terms: two slots at l = 3 (1200 atoms, 1728 points: 0.187 -> 0.134 ms);
+// at l = 4 one slot and three wavefronts (60,000 atoms 6.82 ms, two slots
+// 7.16 ms), the 35 error-free sums being two thirds of the instructions.
+__host__ __device__ constexpr int pass_slots(int mode, int lmax) {
+  return lmax >= 4 ? (mode == ACC_TERMS ? 1 : 2) : (lmax == 3 ? (mode == ACC_TERMS ? 2 : 3) : 4);
 }
 
-template <int MODE, int NM> __device__ inline double acc_value(const Acc<MODE, NM> &a, int m) { return a.value(m); }
+// f(0), .., f(NS - 1) with the index a compile-time constant (register arrays
+// indexed by it stay in registers).
+template <int NS, typename F>
+__device__ inline void for_slots(F &&f) {
+  f(std::integral_constant<int, 0>{});
+  if constexpr (NS > 1) f(std::integral_constant<int, 1>{});
+  if constexpr (NS > 2) f(std::integral_constant<int, 2>{});
+  if constexpr (NS > 3) f(std::integral_constant<int, 3>{});
+}
 
-// Overlap kernel, persistent: every wavefront pulls work items (one chunk
-// of one centre's list) from a global counter until none are left, and
-// walks the sigmas of the item one after another in cutoff order, each over
-// its own prefix of the chunk.  The loads of pair data (j, shift) run two
-// steps ahead and the gathers of the neighbours' wrapped positions one step
-// ahead, continuously across the sigma passes.  Every monomial of degree
-// <= LMAX is accumulated (moments of orders that were not requested are
-// simply not read back).
-//
-// The coefficient table [sigma][element][KB][8] (exponent scale, A_0..A_4,
-// -gamma) is copied into LDS once per workgroup when it fits; lanes read
-// the row of their own neighbour's species.
+// Sum over the two halves of the wavefront of a in lanes 0-31 and of b in
+// lanes 32-63 (one lane swap per 32-bit word).
+__device__ inline double fold32(double a, double b) {
+  const uint64_t ua = __double_as_longlong(a), ub = __double_as_longlong(b);
+  const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)ua, (uint32_t)ub, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(ua >> 32), (uint32_t)(ub >> 32), false, false);
+  return __longlong_as_double(((uint64_t)hi[0] << 32) | lo[0]) + __longlong_as_double(((uint64_t)hi[1] << 32) | lo[1]);
+}
+// Sum over the two 16-lane rows of each half: of a in the even row, of b in the odd one.
+__device__ inline double fold16(double a, double b) {
+  const uint64_t ua = __double_as_longlong(a), ub = __double_as_longlong(b);
+  const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)ua, (uint32_t)ub, false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(ua >> 32), (uint32_t)(ub >> 32), false, false);
+  return __longlong_as_double(((uint64_t)hi[0] << 32) | lo[0]) + __longlong_as_double(((uint64_t)hi[1] << 32) | lo[1]);
+}
+
+// Fixed-order cross-lane sum of NV per-lane doubles, written to dst[0..NV):
+// two folds leave four columns per register (16 partials each), which go
+// through LDS so that one lane sums one column.  A column's 16 partials are
+// 144 bytes apart from the next column's: lanes read from different banks.
+constexpr int kRedStride = 18;
+__host__ __device__ constexpr int red_doubles(int nv) { return ((nv + 3) / 4) * 4 * kRedStride; }
+template <int NV>
+__device__ inline void wave_reduce_store(const double (&v)[NV], double *dst, double *lds) {
+  constexpr int N1 = (NV + 1) / 2, N2 = (N1 + 1) / 2;
+  const int lane = lane_id();
+  double h[N1];
+#pragma unroll
+  for (int r = 0; r < N1; ++r) h[r] = fold32(v[2 * r], 2 * r + 1 < NV ? v[2 * r + 1] : 0.0);
+#pragma unroll
+  for (int r = 0; r < N2; ++r)
+    lds[(4 * r + (lane >> 4)) * kRedStride + (lane & 15)] = fold16(h[2 * r], 2 * r + 1 < N1 ? h[2 * r + 1] : 0.0);
+  wave_lds_sync();
+  if (lane < 4 * N2) {  // register r, row w holds column 4r + 2 (w & 1) + (w >> 1)
+    const double *x = lds + lane * kRedStride;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int t = 0; t < 16; ++t) s[t & 3] += x[t];
+    const int col = (lane & ~3) + 2 * (lane & 1) + ((lane >> 1) & 1);
+    if (col < NV) dst[col] = (s[0] + s[1]) + (s[2] + s[3]);
+  }
+  wave_lds_sync();
+}
+
 // Radial factors c_0..c_L of slot s and element e at squared distance q from
 // the plan's table: cubic in t = r/h - k on interval k of r = sqrt(q).
 template <int L>
@@ -177,74 +207,157 @@ __device__ inline void radial_from_table(const PlanDev &P, int s, int e, float q
   }
 }
 
-// The wide mode's 35 FP64 accumulators and FP64 monomials fit three
-// wavefronts per SIMD (<= 168 VGPRs) once each monomial is accumulated as it
-// is formed; the bound keeps the compiler at that occupancy.
-template <int LMAX, int KB, int MODE, bool LDS, bool DENS, bool SCREEN, bool TAB = false>
-__global__ __launch_bounds__(256, MODE == ACC_WIDE ? 3 : 1) void k_overlap(PlanDev P, BatchDev bt, NbrDev nb, const double4 *rw4,
-                                                 const int32_t *astruct, double *partial, const int64_t *chunk_off,
-                                                 int kc, int ng, unsigned long long *counter,
-                                                 const void *tab_global) {
-  constexpr bool F64 = MODE == ACC_F64;
-  using TR = typename std::conditional<F64, double, float>::type;                 // radial arithmetic
-  using TM = typename std::conditional<MODE == ACC_TWOSUM, float, double>::type;  // monomials
-  constexpr int NM = nmono(LMAX);
+// Squared distance that takes a lane out of a radial sum: far past any
+// cutoff, its exponentials are exact zeros.
+constexpr double kFarQ = 1e30;
+
+// Radial sums c_l += sum_k A_{l,k} exp(-gamma_k q) of NU slots together (NU
+// independent chains per lane).  Table rows past an element's own primitive
+// count are zero (they add exact zeros), so every lane runs the plan's
+// largest count with wavefront-uniform control flow, and the rows k+1 are read
+// before the rows k are used (the empty asm statement keeps the compiler from
+// sinking the reads).
+template <int LMAX, int KB, int NU>
+__device__ inline void radial_sums(const float *const (&row)[NU], const float (&q)[NU], int kmax,
+                                   float (&cl)[NU][LMAX + 1]) {
+  float4 ra[NU];
+  float2 rb[NU];
+#pragma unroll
+  for (int u = 0; u < NU; ++u) { ra[u] = *(const float4 *)row[u]; rb[u] = *(const float2 *)(row[u] + 4); }
+  auto row_step = [&](int k) {
+    float4 na[NU];
+    float2 nb[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+      if (k + 1 < KB) {
+        na[u] = *(const float4 *)(row[u] + (k + 1) * kCoefStride);
+        nb[u] = *(const float2 *)(row[u] + (k + 1) * kCoefStride + 4);
+      }
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const float ek = exp_scaled(ra[u].x, q[u]);
+      const float av[5] = {ra[u].y, ra[u].z, ra[u].w, rb[u].x, rb[u].y};
+#pragma unroll
+      for (int l = 0; l <= LMAX; ++l) cl[u][l] = fma_(av[l], ek, cl[u][l]);
+      if (k + 1 < KB) { ra[u] = na[u]; rb[u] = nb[u]; }
+    }
+  };
+  if constexpr (KB <= 8) {  // full unroll with an early exit (trip count bound <= 8)
+#pragma unroll
+    for (int k = 0; k < KB; ++k) {
+      if (k >= kmax) break;
+      row_step(k);
+    }
+  } else {  // 16-row tables: a wavefront-uniform guard keeps the trip count constant
+#pragma unroll
+    for (int k = 0; k < KB; ++k)
+      if (k < kmax) row_step(k);
+  }
+}
+template <int LMAX, int KB, int NU>
+__device__ inline void radial_sums(const double *const (&row)[NU], const double (&q)[NU], int kmax,
+                                   double (&cl)[NU][LMAX + 1]) {
+  for (int k = 0; k < kmax; ++k) {
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const double *o = row[u] + k * kCoefStride;
+      const double ek = exp_scaled(o[0], q[u]);
+#pragma unroll
+      for (int l = 0; l <= LMAX; ++l) cl[u][l] = fma_(o[1 + l], ek, cl[u][l]);
+    }
+  }
+}
+
+// Overlap kernel, persistent: every wavefront pulls work items (a chunk of
+// one centre's list, for one group of passes) from a global counter until
+// none are left.  A pass takes NS cutoff slots, consecutive in cutoff order,
+// over the longest of their prefixes of the chunk; a slot's part of a step is
+// skipped past its own prefix, for the lanes past it inside the step that
+// straddles it.  The loads of pair data (j, shift) run two steps ahead and
+// the gathers of the neighbours' wrapped positions one step ahead,
+// continuously across the passes.  Moments of orders that were not requested
+// are accumulated and not read back.
+//
+// Bound by VALU issue: 267 instructions per 64 pairs and two slots with
+// harmonics (446 per slot with the error-free FP32 sums of 35 monomials, whose
+// time is that of one pass per slot).  Harmonics against one monomial pass per
+// slot: 512 structures, 3.3e7 pairs, 8 slots, FP32 features alone 1.79 -> 0.95
+// ms; FP32-wide, 192 structures, 0.53 -> 0.39 ms; FP64, 1500 atoms, 0.26 ->
+// 0.17 ms.  Slots of small batches as items of their own: 97 atoms 0.094 ->
+// 0.036 ms.
+//
+// The coefficient table [slot][element][KB][8] (exponent scale, A_0..A_4, ..)
+// is copied into LDS once per workgroup when it fits, with a 16-byte gap
+// after every (slot, element) block: lanes of different species read their
+// rows from different banks.
+template <int LMAX, int KB, int MODE, bool LDS, bool SCREEN, bool OCC, bool TAB = false>
+__global__ __launch_bounds__(256, pass_slots(MODE, LMAX) == 1 ? 3 : 2) void k_overlap(PlanDev P, BatchDev bt, NbrDev nb, const double4 *rw4,
+                                                    const int32_t *astruct, double *partial,
+                                                    const int64_t *chunk_off, int kc, int ng,
+                                                    int nbatch, unsigned long long *counter, const void *tab_global) {
+  using TR = typename std::conditional<MODE == ACC_F64, double, float>::type;  // radial arithmetic
+  constexpr int NH = n_moments(MODE, LMAX), NS = pass_slots(MODE, LMAX);
+  constexpr int BLK = KB * kCoefStride, BLKL = BLK + 16 / (int)sizeof(TR);
   extern __shared__ __align__(16) double lds_dyn[];
-  __shared__ double lds_red[4][64 * 9];
-  __shared__ int lds_k[kMaxElements];
+  __shared__ __align__(16) double lds_red[4][red_doubles(NH)];
   const int S = P.S, E = P.E;
   const TR *__restrict__ tabg = (const TR *)tab_global;
   TR *tabl = (TR *)lds_dyn;
   if (LDS) {
-    const int n = S * E * KB * kCoefStride;
-    for (int idx = threadIdx.x; idx < n; idx += blockDim.x) tabl[idx] = tabg[idx];
+    const int n = S * E * BLK;
+    for (int idx = threadIdx.x; idx < n; idx += blockDim.x) tabl[(idx / BLK) * BLKL + idx % BLK] = tabg[idx];
   }
-  for (int e = threadIdx.x; e < E; e += blockDim.x) lds_k[e] = P.kcount[e];
   __syncthreads();
 
   const int lane = lane_id();
   const int wv = threadIdx.x / kWave;
   const int64_t N = n_centres(bt), cb = centre_base(bt);
-  const int64_t n_items = chunk_off[N];
-  for (;;) {
-    const int64_t qc = next_item(counter);
-    if (qc >= n_items) break;
+  const int64_t n_items = chunk_off[N] * ng;
+  const int NP = (S + NS - 1) / NS;
+  auto table_row = [&](int s, int e) -> const TR * {
+    return LDS ? tabl + s * E * BLKL + __umul24(e, BLKL) : tabg + (size_t)(s * E + e) * BLK;
+  };
+  for (int64_t item = 0, left = 0;; ++item, --left) {
+    if (left == 0) {
+      item = next_item(counter) * nbatch;
+      left = nbatch;
+    }
+    if (item >= n_items) break;
+    // item = (chunk qc, group g of its passes: [t0, t1)); every item writes
+    // the moments of its own slots, so the rows are the same for any ng
+    const int64_t qc = item / ng;
+    const int g = (int)(item - qc * ng);
+    const int t0 = g * NP / ng, t1 = (g + 1) * NP / ng;
     const int64_t k = centre_of_chunk(chunk_off, N, qc);  // list slot
     const int64_t i = nb.order[k];                         // its centre
-    // item = (chunk c of the list, group g of the cutoff slots in cutoff
-    // order: passes [t0, t1)); every item writes all slots' moments, zero
-    // for the slots outside its group, so a centre's sum is the same for any ng
-    const int cg = (int)(qc - chunk_off[k]);
-    const int c = cg / ng, g = cg - c * ng;
-    const int t0 = g * S / ng, t1 = (g + 1) * S / ng;
+    const int c = (int)(qc - chunk_off[k]);
     const int st = astruct[cb + i];
     const Cell9 cell = load_cell(bt.cell + 9 * (int64_t)st);
     const int pbc = bt.pbc[st] & 7;
     const double4 ri4 = rw4[cb + i];
     const double rix = ri4.x, riy = ri4.y, riz = ri4.z;
-    const int64_t base = nb.offsets[k];
-    const int cnt = (int)(nb.offsets[k + 1] - base);
+    const int64_t base = uniform64(nb.offsets[k]);
+    const int cnt = (int)(uniform64(nb.offsets[k + 1]) - base);
     const int clo = kc > 0 ? c * kc : 0;
     const int chi = kc > 0 ? (clo + kc < cnt ? clo + kc : cnt) : cnt;
-    // per-item pass ends and sigma order, one per lane (lane t <-> t-th sigma by cutoff)
+    // prefix ends inside the chunk and slots by cutoff order, one per lane
     int end_lane = clo, so_lane = 0;
     if (lane < S) {
       so_lane = P.sig_order[lane];
       const int en = nb.sigma_end[k * S + so_lane];
-      end_lane = en < chi ? en : chi;
+      end_lane = en < clo ? clo : (en < chi ? en : chi);
     }
     auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
-    auto pass_end = [&](int t) { return __builtin_amdgcn_readlane(end_lane, t); };
-    double *dst_item = partial + (size_t)qc * S * NM;
-    // sigmas outside the item's group, or whose prefix misses this chunk,
-    // contribute zero moments
-    for (int t = 0; t < S; ++t)
-      if (t < t0 || t >= t1 || pass_end(t) <= clo)
-        for (int m = lane; m < NM; m += kWave)
-          dst_item[(size_t)__builtin_amdgcn_readlane(so_lane, t) * NM + m] = 0.0;
-    // step iterator over (sigma pass t, pair block p0); pass ends are non-decreasing in t
+    auto slot_end = [&](int t) { return __builtin_amdgcn_readlane(end_lane, t); };
+    auto pass_end = [&](int t) { return slot_end(t * NS + NS - 1 < S ? t * NS + NS - 1 : S - 1); };
+    double *dst_item = partial + (size_t)qc * S * NH;
+    // passes whose prefixes miss this chunk contribute zero moments (pass
+    // ends are non-decreasing: they come first)
     int tb = t0, pb = clo;
     while (tb < t1 && pass_end(tb) <= clo) ++tb;
+    for (int t = t0 * NS; t < tb * NS && t < S; ++t)
+      for (int m = lane; m < NH; m += kWave) dst_item[(size_t)__builtin_amdgcn_readlane(so_lane, t) * NH + m] = 0.0;
     if (tb >= t1) continue;
     int tc = tb, pc = pb;
     auto advance = [&](int &t, int &p) {
@@ -252,7 +365,6 @@ __global__ __launch_bounds__(256, MODE == ACC_WIDE ? 3 : 1) void k_overlap(PlanD
       if (p >= pass_end(t)) {
         ++t;
         p = clo;
-        while (t < t1 && pass_end(t) <= clo) ++t;
       }
       t = uni(t);
       p = uni(p);
@@ -269,148 +381,139 @@ __global__ __launch_bounds__(256, MODE == ACC_WIDE ? 3 : 1) void k_overlap(PlanD
       if (tc < t1 && pc + lane < pass_end(tc)) { jc = nb.j[base + pc + lane]; wc = nb.shift[base + pc + lane]; }
       rb = rw4[jb];
     }
-    Acc<MODE, NM> acc;
-    acc.zero();
+    Acc<MODE, NH> acc[NS];
+#pragma unroll
+    for (int u = 0; u < NS; ++u) acc[u].zero();
     while (tb < t1) {
       const int ta = tb, pa = pb;
-      const int32_t w = wb;
-      const double rjx = rb.x, rjy = rb.y, rjz = rb.z, occj = rb.w;  // w: occupancy of j
-      // advance the pipeline
+      // the current step's pair, from what the pipeline holds
+      const int p = pa + lane;
+      double shx = 0.0, shy = 0.0, shz = 0.0;
+      if (pbc) image_shift(cell, shift_n(wb, 0), shift_n(wb, 1), shift_n(wb, 2), shx, shy, shz);
+      double dx = (rb.x - rix) + shx;
+      double dy = (rb.y - riy) + shy;
+      double dz = (rb.z - riz) + shz;
+      double occj = rb.w;
+      int e = shift_species(wb);
+      // advance the pipeline.  The asm statements pin these values here, ahead
+      // of the new loads, which then go into the registers they came from:
+      // loaded into others, they would be waited for and copied at the end of
+      // this same step.
+      asm volatile("" : "+v"(dx), "+v"(dy), "+v"(dz), "+v"(e));
+      if constexpr (OCC || MODE == ACC_TERMS) asm volatile("" : "+v"(occj));
       tb = tc; pb = pc; wb = wc;
-      rb = rw4[jc];
+      int32_t jn = jc;
+      asm volatile("" : "+v"(wb), "+v"(jn));
+      rb = rw4[jn];
       jc = ii; wc = 0;
       if (tc < t1) {
         advance(tc, pc);
         if (tc < t1 && pc + lane < pass_end(tc)) { jc = nb.j[base + pc + lane]; wc = nb.shift[base + pc + lane]; }
       }
-      // current step: slot sig_order[ta], pairs pa + lane
-      const int sgm = __builtin_amdgcn_readlane(so_lane, ta);
-      const int p = pa + lane;
-      if (DENS && p < pass_end(ta) && sgm == P.dens_slot) {
-        // local density (order -1): the degree-0 moment of sum_k B exp(-beta q)
-        double shx = 0.0, shy = 0.0, shz = 0.0;
-        if (pbc) image_shift(cell, shift_n(w, 0), shift_n(w, 1), shift_n(w, 2), shx, shy, shz);
-        const double dx = (rjx - rix) + shx;
-        const double dy = (rjy - riy) + shy;
-        const double dz = (rjz - riz) + shz;
-        const double q = (dx * dx + dy * dy) + dz * dz;
-        const TR qv = (TR)q;
-        const int e = shift_species(w);
-        const int K = TAB ? 0 : lds_k[e];
-        const size_t roff = ((size_t)(sgm * E + e) * KB) * kCoefStride;
-        TR c0 = (TR)0;
-        if constexpr (TAB && !F64) {
-          float ct[1];
-          radial_from_table<0>(P, sgm, e, qv, ct);
-          c0 = ct[0];
-        }
+      const double q = (dx * dx + dy * dy) + dz * dz;
+      const TR qv = (TR)q;
+      auto step = [&] {
+        // radial factors of the pass's slots; zero past a slot's own prefix
+        TR cl[NS][LMAX + 1];
+        const int tl = ta * NS;
+        if (NS > 1 && !SCREEN && !TAB && tl + NS <= S && pa < slot_end(tl)) {  // every slot takes pairs of this step
+          const TR *row[NS];
+          TR qu[NS];
 #pragma unroll
-        for (int k = 0; k < KB; ++k) {
-          if (k < K) {
-            const size_t o = roff + k * kCoefStride;
-            bool use = true;
-            if constexpr (SCREEN) {  // the primitive's own radius; skipped by the wavefront when no lane needs it
-              use = (float)q <= (float)(LDS ? tabl[o + 7] : tabg[o + 7]);
-              if (__ballot(use) == 0) continue;
-            }
-            const TR ek = exp_scaled(LDS ? tabl[o] : tabg[o], qv);
-            c0 = fma_(LDS ? tabl[o + 1] : tabg[o + 1], use ? ek : (TR)0, c0);
+          for (int u = 0; u < NS; ++u) {
+            row[u] = table_row(__builtin_amdgcn_readlane(so_lane, tl + u), e);
+            qu[u] = p < slot_end(tl + u) ? qv : (TR)kFarQ;
+#pragma unroll
+            for (int l = 0; l <= LMAX; ++l) cl[u][l] = (TR)0;
           }
-        }
-        c0 = c0 * (TR)occj;
-        if constexpr (MODE == ACC_TWOSUM) acc.add(0, c0);
-        else acc.v[0] += (double)c0;
-      } else if (p < pass_end(ta)) {
-        double shx = 0.0, shy = 0.0, shz = 0.0;
-        if (pbc) image_shift(cell, shift_n(w, 0), shift_n(w, 1), shift_n(w, 2), shx, shy, shz);
-        const double dx = (rjx - rix) + shx;
-        const double dy = (rjy - riy) + shy;
-        const double dz = (rjz - riz) + shz;
-        const double q = (dx * dx + dy * dy) + dz * dz;
-        const TR qv = (TR)q;
-        const int e = shift_species(w);
-        const int K = lds_k[e];
-        const size_t roff = ((size_t)(sgm * E + e) * KB) * kCoefStride;
-        TR cl[LMAX + 1];
+          radial_sums<LMAX, KB, NS>(row, qu, P.kmax, cl);
+        } else {
+          auto slot_radial = [&](auto uc) {
+            constexpr int u = decltype(uc)::value;
 #pragma unroll
-        for (int l = 0; l <= LMAX; ++l) cl[l] = (TR)0;
-        if constexpr (TAB && !F64) {
-          radial_from_table<LMAX>(P, sgm, e, qv, cl);
-        } else if constexpr (!SCREEN && !F64) {
-          // FP32 table rows past an element's own primitive count are zero
-          // (they add exact zeros), so every lane runs the plan's largest
-          // count with wavefront-uniform control flow, and the LDS read of
-          // row k+1 is issued before row k is used (the empty asm statement
-          // keeps the compiler from sinking it)
-          const TR *row = (LDS ? tabl : tabg) + roff;
-          const int kmx = P.kmax;
-          float4 ra = *(const float4 *)row;
-          float2 rb2 = *(const float2 *)(row + 4);
-          auto row_step = [&](int k) {
-            float4 na; float2 nb2;
-            if (k + 1 < KB) { na = *(const float4 *)(row + (k + 1) * kCoefStride); nb2 = *(const float2 *)(row + (k + 1) * kCoefStride + 4); }
-            asm volatile("" ::: "memory");
-            const TR ek = exp_scaled(ra.x, qv);
-            const TR av[5] = {ra.y, ra.z, ra.w, rb2.x, rb2.y};
+            for (int l = 0; l <= LMAX; ++l) cl[u][l] = (TR)0;
+            const int t = tl + u;
+            if (NS > 1 && (t >= S || p >= slot_end(t))) return;
+            const int sgm = __builtin_amdgcn_readlane(so_lane, t);
+            if constexpr (TAB) {
+              radial_from_table<LMAX>(P, sgm, e, qv, cl[u]);
+            } else {
+              const TR *row[1] = {table_row(sgm, e)};
+              if constexpr (SCREEN) {
+                // the primitive's own radius; skipped by the wavefront when no lane needs it
 #pragma unroll
-            for (int l = 0; l <= LMAX; ++l) cl[l] = fma_(av[l], ek, cl[l]);
-            if (k + 1 < KB) { ra = na; rb2 = nb2; }
-          };
-          if constexpr (KB <= 8) {  // full unroll with an early exit (trip count bound <= 8)
+                for (int k = 0; k < KB; ++k) {
+                  if (k < P.kmax) {
+                    const TR *o = row[0] + k * kCoefStride;
+                    const bool use = (float)q <= (float)o[7];
+                    if (__ballot(use) == 0) continue;
+                    const TR ek = use ? exp_scaled(o[0], qv) : (TR)0;
 #pragma unroll
-            for (int k = 0; k < KB; ++k) {
-              if (k >= kmx) break;
-              row_step(k);
+                    for (int l = 0; l <= LMAX; ++l) cl[u][l] = fma_(o[1 + l], ek, cl[u][l]);
+                  }
+                }
+              } else {
+                const TR qu[1] = {qv};
+                TR c1[1][LMAX + 1];
+#pragma unroll
+                for (int l = 0; l <= LMAX; ++l) c1[0][l] = (TR)0;
+                radial_sums<LMAX, KB, 1>(row, qu, P.kmax, c1);
+#pragma unroll
+                for (int l = 0; l <= LMAX; ++l) cl[u][l] = c1[0][l];
+              }
             }
-          } else {  // 16-row tables: a wavefront-uniform guard keeps the trip count constant
+          };
+          for_slots<NS>(slot_radial);
+        }
+        // harmonics (monomials), each accumulated for every slot of the pass as it is formed
+        auto is_density = [&](int u) {
+          return tl + u < S && __builtin_amdgcn_readlane(so_lane, tl + u < S ? tl + u : 0) == P.dens_slot;
+        };
+        if constexpr (MODE == ACC_TERMS) {
+          float mono[NH];
+          const float xv = (float)dx, yv = (float)dy, zv = (float)dz;
+          mono[0] = (float)occj;  // the occupancy scales every monomial of the pair
 #pragma unroll
-            for (int k = 0; k < KB; ++k)
-              if (k < kmx) row_step(k);
+          for (int u = 0; u < NS; ++u) acc[u].add(0, cl[u][0] * mono[0]);
+          if (NS > 1 || !is_density(0)) {
+#pragma unroll
+            for (int m = 1; m < NH; ++m) {
+              mono[m] = (kMT.var[m] == 0 ? xv : (kMT.var[m] == 1 ? yv : zv)) * mono[kMT.parent[m]];
+#pragma unroll
+              for (int u = 0; u < NS; ++u) acc[u].add(m, cl[u][kMT.deg[m]] * mono[m]);
+            }
           }
         } else {
+          if constexpr (OCC && MODE == ACC_WIDE) {  // the density is scaled in FP32, as its FP32 sum is
 #pragma unroll
-        for (int k = 0; k < KB; ++k) {
-          if (k < K) {
-            const size_t o = roff + k * kCoefStride;
-            bool use = true;
-            if constexpr (SCREEN) {  // the primitive's own radius; skipped by the wavefront when no lane needs it
-              use = (float)q <= (float)(LDS ? tabl[o + 7] : tabg[o + 7]);
-              if (__ballot(use) == 0) continue;
+            for (int u = 0; u < NS; ++u) cl[u][0] *= is_density(u) ? (float)occj : 1.f;
+          }
+          for_harmonics<LMAX, true>(dx, dy, dz, [&](auto mc, double Y) {
+            constexpr int m = decltype(mc)::value;
+#pragma unroll
+            for (int u = 0; u < NS; ++u) {
+              double c = (double)cl[u][hdeg(m)];
+              if constexpr (OCC) c *= MODE == ACC_WIDE && m == 0 && is_density(u) ? 1.0 : occj;
+              acc[u].v[m] = m == 0 ? acc[u].v[m] + c : fma(c, Y, acc[u].v[m]);
             }
-            TR ek = exp_scaled(LDS ? tabl[o] : tabg[o], qv);
-            if constexpr (SCREEN) ek = use ? ek : (TR)0;
+          });
+        }
+      };
+      // one slot: lanes past its prefix sit out; several: they take zeros
+      if (NS > 1 || p < slot_end(ta * NS)) step();
+      if (tb != ta) {  // the pass is complete: cross-lane reductions, store, restart
+        auto slot_store = [&](auto uc) {
+          constexpr int u = decltype(uc)::value;
+          const int t = ta * NS + u;
+          if (t < S) {
+            double v[NH];
 #pragma unroll
-            for (int l = 0; l <= LMAX; ++l) cl[l] = fma_(LDS ? tabl[o + 1 + l] : tabg[o + 1 + l], ek, cl[l]);
+            for (int m = 0; m < NH; ++m) v[m] = acc[u].value(m);
+            wave_reduce_store<NH>(v, dst_item + (size_t)__builtin_amdgcn_readlane(so_lane, t) * NH, lds_red[wv]);
           }
-        }
-        }
-        // monomials degree by degree from their parents, each accumulated as
-        // soon as it is formed (only the previous degree's stay live)
-        double cd[LMAX + 1];
-        if constexpr (MODE != ACC_TWOSUM) {
-#pragma unroll
-          for (int l = 0; l <= LMAX; ++l) cd[l] = (double)cl[l];
-        }
-        TM mono[NM];
-        const TM xv = (TM)dx, yv = (TM)dy, zv = (TM)dz;
-#pragma unroll
-        for (int m = 0; m < NM; ++m) {
-          if (m == 0) {
-            mono[0] = (TM)occj;  // the occupancy scales every monomial of the pair
-          } else {
-            const TM v = kMT.var[m] == 0 ? xv : (kMT.var[m] == 1 ? yv : zv);
-            mono[m] = v * mono[kMT.parent[m]];
-          }
-          if constexpr (MODE == ACC_TWOSUM) acc.add(m, cl[kMT.deg[m]] * mono[m]);
-          else acc.v[m] = fma(cd[kMT.deg[m]], mono[m], acc.v[m]);
-        }
-      }
-      if (tb != ta) {  // the pass of slot sgm is complete: FP64 cross-lane reduction, store, restart
-        double vals[NM];
-#pragma unroll
-        for (int m = 0; m < NM; ++m) vals[m] = acc.value(m);
-        wave_reduce_store<NM>(vals, dst_item + (size_t)sgm * NM, lds_red[wv]);
-        acc.zero();
+          acc[u].zero();
+        };
+        for_slots<NS>(slot_store);
       }
     }
   }
@@ -424,16 +527,17 @@ __global__ __launch_bounds__(256, MODE == ACC_WIDE ? 3 : 1) void k_overlap(PlanD
 // decoded once per workgroup into LDS tables, so the per-centre loops are
 // table reads and dot products; the partials of a centre with one work item
 // (the common case) are read directly.
-template <int LMAX, bool F64OUT>
+template <int LMAX, bool F64OUT, bool MONO>
 __global__ __launch_bounds__(256) void k_finish(PlanDev P, int64_t N, const double *partial,
                                                 const int64_t *chunk_off, const int32_t *order, void *features,
                                                 double *components) {
   extern __shared__ double lds_f[];
   // moment -> component maps of all orders and the multinomial weights,
   // staged in LDS once per workgroup (read with lane-varying indices)
-  __shared__ double lds_T[kTmat];
+  constexpr int NT = MONO ? kTmat : kHmat;
+  __shared__ double lds_T[NT];
   __shared__ double lds_w[nmono(kMaxL)];
-  constexpr int NM = nmono(LMAX);  // compile-time: the index splits below are not divisions
+  constexpr int NM = MONO ? nmono(LMAX) : nharm(LMAX);  // compile-time: the index splits below are not divisions
   const int S = P.S, NC = P.ncomp_total, NF = P.nf;
   // decode tables after the four wavefronts' moment and component buffers:
   // component t: T row offset | moment offset << 10 | length << 22 (bit 31:
@@ -441,7 +545,7 @@ __global__ __launch_bounds__(256) void k_finish(PlanDev P, int64_t N, const doub
   // weight offset << 12 | length << 20 (bit 31: the density feature)
   int32_t *cdec = (int32_t *)(lds_f + (size_t)4 * (S * NM + NC));
   int32_t *fdec = cdec + NC;
-  for (int t = threadIdx.x; t < kTmat; t += blockDim.x) lds_T[t] = P.T[t];
+  for (int t = threadIdx.x; t < NT; t += blockDim.x) lds_T[t] = MONO ? P.T[t] : P.H[t];
   for (int t = threadIdx.x; t < nmono(kMaxL); t += blockDim.x) lds_w[t] = P.weight[t];
   for (int t = threadIdx.x; t < NC; t += blockDim.x) {
     int o = 0;
@@ -452,7 +556,8 @@ __global__ __launch_bounds__(256) void k_finish(PlanDev P, int64_t N, const doub
     } else {
       const int nc = ncomp(l), r = t - P.comp_off[o];
       const int sl = r / nc, cc = r - sl * nc;
-      cdec[t] = (P.toff[l] + cc * nc) | ((sl * NM + doff(l)) << 10) | (nc << 22);
+      const int nm = MONO ? nc : 2 * l + 1;  // moments of degree l
+      cdec[t] = ((MONO ? P.toff[l] : P.hoff[l]) + cc * nm) | ((sl * NM + (MONO ? doff(l) : l * l)) << 10) | (nm << 22);
     }
   }
   for (int t = threadIdx.x; t < NF; t += blockDim.x) {
@@ -476,14 +581,11 @@ __global__ __launch_bounds__(256) void k_finish(PlanDev P, int64_t N, const doub
   if (live) {
     const int64_t q0 = chunk_off[i], q1 = chunk_off[i + 1];
     for (int t = lane; t < S * NM; t += kWave) {
-      const int s = t / NM, m = t - s * NM;
       double a = 0.0;
-      if (s == P.dens_slot ? m == 0 : ((P.order_mask >> kMT.deg[m]) & 1)) {
-        if (q1 - q0 == 1) {
-          a = partial[((size_t)q0 * S + s) * NM + m];
-        } else {
-          for (int64_t q = q0; q < q1; ++q) a += partial[((size_t)q * S + s) * NM + m];
-        }
+      if (q1 - q0 == 1) {
+        a = partial[(size_t)q0 * S * NM + t];
+      } else {
+        for (int64_t q = q0; q < q1; ++q) a += partial[(size_t)q * S * NM + t];
       }
       mom[t] = a;
     }
@@ -527,51 +629,46 @@ __global__ __launch_bounds__(256) void k_finish(PlanDev P, int64_t N, const doub
 }
 
 using OverlapFn = void (*)(PlanDev, BatchDev, NbrDev, const double4 *, const int32_t *, double *, const int64_t *,
-                           int, int, unsigned long long *, const void *);
+                           int, int, int, unsigned long long *, const void *);
 
-// DENS: the plan has the density slot of order -1; SCREEN: per-primitive
-// screening (separate instantiations keep both branches out of the loop of
-// plans without them)
-template <int L, int MODE, bool LDS, bool DENS, bool SCREEN> OverlapFn pick_k(int kb) {
-  if (kb <= 4) return k_overlap<L, 4, MODE, LDS, DENS, SCREEN>;
-  if (kb <= 8) return k_overlap<L, 8, MODE, LDS, DENS, SCREEN>;
-  return k_overlap<L, 16, MODE, LDS, DENS, SCREEN>;
+// SCREEN: per-primitive screening; OCC: the neighbours' occupancies scale the
+// terms (without occupancies they are 1, so the variants that are not on the
+// common path always multiply)
+template <int L, int MODE, bool LDS, bool SCREEN, bool OCC> OverlapFn pick_k(int kb) {
+  if (kb <= 4) return k_overlap<L, 4, MODE, LDS, SCREEN, OCC>;
+  if (kb <= 8) return k_overlap<L, 8, MODE, LDS, SCREEN, OCC>;
+  return k_overlap<L, 16, MODE, LDS, SCREEN, OCC>;
 }
-
-template <int MODE, bool LDS, bool DENS, bool SCREEN> OverlapFn pick_l(int lmax, int kb) {
+template <int MODE, bool LDS, bool SCREEN, bool OCC> OverlapFn pick_l(int lmax, int kb) {
   switch (lmax) {
-    case 0: return pick_k<0, MODE, LDS, DENS, SCREEN>(kb);
-    case 1: return pick_k<1, MODE, LDS, DENS, SCREEN>(kb);
-    case 2: return pick_k<2, MODE, LDS, DENS, SCREEN>(kb);
-    case 3: return pick_k<3, MODE, LDS, DENS, SCREEN>(kb);
-    default: return pick_k<4, MODE, LDS, DENS, SCREEN>(kb);
+    case 0: return pick_k<0, MODE, LDS, SCREEN, OCC>(kb);
+    case 1: return pick_k<1, MODE, LDS, SCREEN, OCC>(kb);
+    case 2: return pick_k<2, MODE, LDS, SCREEN, OCC>(kb);
+    case 3: return pick_k<3, MODE, LDS, SCREEN, OCC>(kb);
+    default: return pick_k<4, MODE, LDS, SCREEN, OCC>(kb);
   }
 }
-
-template <bool LDS, bool DENS, bool SCREEN> OverlapFn pick_d(gmp_precision prec, int lmax, int kb) {
-  if (prec == GMP_FP64) return pick_l<ACC_F64, LDS, DENS, SCREEN>(lmax, kb);
-  if (prec == GMP_FP32_WIDE) return pick_l<ACC_WIDE, LDS, DENS, SCREEN>(lmax, kb);
-  return pick_l<ACC_TWOSUM, LDS, DENS, SCREEN>(lmax, kb);
+template <int MODE> OverlapFn pick_overlap(int lmax, int kb, bool lds, bool screen, bool occ) {
+  if (screen) return lds ? pick_l<MODE, true, true, true>(lmax, kb) : pick_l<MODE, false, true, true>(lmax, kb);
+  if (!lds) return pick_l<MODE, false, false, true>(lmax, kb);
+  if constexpr (MODE == ACC_TERMS) return pick_l<MODE, true, false, true>(lmax, kb);
+  else return occ ? pick_l<MODE, true, false, true>(lmax, kb) : pick_l<MODE, true, false, false>(lmax, kb);
 }
 
 // tabulated radial factors (FP32 modes): no coefficient table, no primitive loop
-template <int MODE, bool DENS> OverlapFn pick_tab_l(int lmax) {
+template <int MODE> OverlapFn pick_tab(int lmax) {
   switch (lmax) {
-    case 0: return k_overlap<0, 4, MODE, false, DENS, false, true>;
-    case 1: return k_overlap<1, 4, MODE, false, DENS, false, true>;
-    case 2: return k_overlap<2, 4, MODE, false, DENS, false, true>;
-    case 3: return k_overlap<3, 4, MODE, false, DENS, false, true>;
-    default: return k_overlap<4, 4, MODE, false, DENS, false, true>;
+    case 0: return k_overlap<0, 4, MODE, false, false, true, true>;
+    case 1: return k_overlap<1, 4, MODE, false, false, true, true>;
+    case 2: return k_overlap<2, 4, MODE, false, false, true, true>;
+    case 3: return k_overlap<3, 4, MODE, false, false, true, true>;
+    default: return k_overlap<4, 4, MODE, false, false, true, true>;
   }
 }
-OverlapFn pick_tab(gmp_precision prec, int lmax, bool dens) {
-  if (prec == GMP_FP32_WIDE) return dens ? pick_tab_l<ACC_WIDE, true>(lmax) : pick_tab_l<ACC_WIDE, false>(lmax);
-  return dens ? pick_tab_l<ACC_TWOSUM, true>(lmax) : pick_tab_l<ACC_TWOSUM, false>(lmax);
-}
 
-template <bool LDS> OverlapFn pick_m(gmp_precision prec, int lmax, int kb, bool dens, bool screen) {
-  if (screen) return dens ? pick_d<LDS, true, true>(prec, lmax, kb) : pick_d<LDS, false, true>(prec, lmax, kb);
-  return dens ? pick_d<LDS, true, false>(prec, lmax, kb) : pick_d<LDS, false, false>(prec, lmax, kb);
+int acc_mode(const gmp_plan *p, bool components) {
+  if (p->prec == GMP_FP64) return ACC_F64;
+  return p->prec == GMP_FP32_COMPENSATED && components ? ACC_TERMS : ACC_WIDE;
 }
 
 }  // namespace
@@ -606,16 +703,34 @@ void *noalloc_scratch(size_t *bytes, hipError_t *err) {
 
 int chunk_size(const gmp_plan *p) { return p->tuning.chunk_pairs > 0 ? p->tuning.chunk_pairs : 0; }
 
-// groups of cutoff slots per chunk (each a work item of its own)
+// groups of cutoff slots per chunk that the tuning asks for
 int slot_groups(const gmp_plan *p) {
   const int g = p->tuning.sigma_groups > 0 ? p->tuning.sigma_groups : 1;
   return g < p->dev.S ? g : (p->dev.S > 0 ? p->dev.S : 1);
 }
 
-// upper bound on the number of work items of a batch with at most `pairs` pairs
-int64_t max_chunks(const gmp_plan *p, int64_t n_atoms, int64_t pairs) {
+// upper bound on the number of chunks of a batch with at most `pairs` pairs
+static int64_t chunks_bound(const gmp_plan *p, int64_t n_atoms, int64_t pairs) {
   const int kc = chunk_size(p);
-  return (n_atoms + (kc > 0 ? pairs / kc + 1 : 0)) * slot_groups(p);
+  return n_atoms + (kc > 0 ? pairs / kc + 1 : 0);
+}
+
+// rows of partial moments a batch is given room for
+int64_t max_chunks(const gmp_plan *p, int64_t n_atoms, int64_t pairs) {
+  return chunks_bound(p, n_atoms, pairs) * slot_groups(p);
+}
+
+// Groups of passes per chunk (each a work item of its own): what the tuning
+// asks for, and more where the centres alone leave wavefronts idle: towards
+// 8,192 items, some four for each wavefront of the chip at two per SIMD (FP64,
+// 1500 atoms: 0.187 ms aiming at 4,096, 0.173 at 8,192); 4,096 with the longer
+// items of FP32 terms (4096 atoms: 0.396 ms, 0.420 aiming at 8,192).
+static int item_groups(const gmp_plan *p, int64_t n_centres, int mode, int passes) {
+  int64_t g = slot_groups(p);
+  const int64_t aim = mode == ACC_TERMS ? 4096 : 8192;
+  const int64_t want = (aim + n_centres - 1) / n_centres;
+  if (g < want) g = want;
+  return (int)(g < passes ? g : passes);
 }
 
 static int cus_cached() {
@@ -649,45 +764,59 @@ int persistent_blocks(const void *fn, size_t smem, int blocks_per_cu) {
 
 void launch_overlap(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, double *partial, int64_t *nch,
                     int64_t *chunk_off, int64_t *scan_aux, unsigned long long *counter, double4 *rw4,
-                    int32_t *astruct, int64_t pairs_bound, hipStream_t s) {
+                    int32_t *astruct, int64_t pairs_bound, bool components, hipStream_t s) {
   const int64_t N = n_centres(bt), NT = n_total(bt);  // NT >= N
-  const int kc = chunk_size(p), ng = slot_groups(p);
-  GMP_LAUNCH("overlap_prep", k_overlap_prep, dim3((unsigned)((NT + 255) / 256)), dim3(256), 0, s, bt, nb, kc, ng,
-             nch, rw4, astruct, counter);
+  const int kc = chunk_size(p);
+  GMP_LAUNCH("overlap_prep", k_overlap_prep, dim3((unsigned)((NT + 255) / 256)), dim3(256), 0, s, bt, nb, kc, nch, rw4,
+             astruct, counter);
   scan_i64(nch, chunk_off, N, scan_aux, s);
-  const bool f64 = p->prec == GMP_FP64;
+  const int lmax = p->dev.lmax, mode = acc_mode(p, components), slots = pass_slots(mode, lmax);
+  const int passes = (p->dev.S + slots - 1) / slots, ng = item_groups(p, N, mode, passes);
+  const bool f64 = mode == ACC_F64;
   const size_t tab_bytes = (size_t)p->dev.S * p->dev.E * p->dev.kb * kCoefStride * (f64 ? 8 : 4);
   const bool tabulated = p->dev.tab_n > 0 && !f64;
   const bool use_lds = tab_bytes <= 48 * 1024 && !tabulated;
-  const size_t smem = use_lds ? tab_bytes : 0;
+  const size_t smem = use_lds ? tab_bytes + (size_t)p->dev.S * p->dev.E * 16 : 0;  // with its gaps
   const void *tab = f64 ? (const void *)p->dev.coef64 : (const void *)p->dev.coef32;
-  const bool dens = p->dev.dens_slot >= 0;
-  const bool screen = p->dev.screen != 0;
-  OverlapFn fn = tabulated ? pick_tab(p->prec, p->dev.lmax, dens)
-                 : use_lds ? pick_m<true>(p->prec, p->dev.lmax, p->dev.kb, dens, screen)
-                           : pick_m<false>(p->prec, p->dev.lmax, p->dev.kb, dens, screen);
-  const int64_t items_bound = max_chunks(p, N, pairs_bound);
+  const bool screen = p->dev.screen != 0, occ = bt.occ != nullptr;
+  const int kb = p->dev.kb;
+  OverlapFn fn = tabulated ? (mode == ACC_TERMS ? pick_tab<ACC_TERMS>(lmax) : pick_tab<ACC_WIDE>(lmax))
+                 : f64     ? pick_overlap<ACC_F64>(lmax, kb, use_lds, screen, occ)
+                 : mode == ACC_TERMS ? pick_overlap<ACC_TERMS>(lmax, kb, use_lds, screen, occ)
+                                     : pick_overlap<ACC_WIDE>(lmax, kb, use_lds, screen, occ);
+  const int64_t items_bound = chunks_bound(p, N, pairs_bound) * ng;
   int64_t blocks = persistent_blocks((const void *)fn, smem, p->tuning.blocks_per_cu);
   const int64_t need = (items_bound + 3) / 4;
   if (blocks > need) blocks = need;
   if (blocks < 1) blocks = 1;
+  // Items per request to the counter: requests from all wavefronts to one
+  // address are served one after another, some 12 ns each (146,000 items of
+  // the 512-structure batch took 1.83 ms one by one, 0.95 ms as 36,600), so
+  // where a wavefront gets many items it takes several at a time, few enough
+  // that the launch's end stays balanced.
+  int64_t nbatch = N * ng / (blocks * 4 * 16);
+  nbatch = nbatch < 1 ? 1 : (nbatch > 8 ? 8 : nbatch);
   GMP_LAUNCH("overlap", fn, dim3((unsigned)blocks), dim3(256), smem, s, p->dev, bt, nb, (const double4 *)rw4,
-             (const int32_t *)astruct, partial, chunk_off, kc, ng, counter, tab);
+             (const int32_t *)astruct, partial, chunk_off, kc, ng, (int)nbatch, counter, tab);
 }
 
 void launch_finish(const gmp_plan *p, int64_t N, const double *partial, const int64_t *chunk_off,
                    const int32_t *order, void *features, double *components, hipStream_t s) {
   if (N == 0) return;
-  const int NM = nmono(p->dev.lmax);
+  const int mode = acc_mode(p, components != nullptr), NM = n_moments(mode, p->dev.lmax);
   size_t smem = sizeof(double) * 4 * (size_t)(p->dev.S * NM + p->dev.ncomp_total) +
                 sizeof(int32_t) * (size_t)(p->dev.ncomp_total + p->dev.nf);  // + the decode tables
   int64_t blocks = (N + 3) / 4;
   using FinishFn = void (*)(PlanDev, int64_t, const double *, const int64_t *, const int32_t *, void *, double *);
-  static const FinishFn fns[2][kMaxL + 1] = {
-      {k_finish<0, false>, k_finish<1, false>, k_finish<2, false>, k_finish<3, false>, k_finish<4, false>},
-      {k_finish<0, true>, k_finish<1, true>, k_finish<2, true>, k_finish<3, true>, k_finish<4, true>}};
+  static const FinishFn fns[3][kMaxL + 1] = {
+      {k_finish<0, true, false>, k_finish<1, true, false>, k_finish<2, true, false>, k_finish<3, true, false>,
+       k_finish<4, true, false>},
+      {k_finish<0, false, false>, k_finish<1, false, false>, k_finish<2, false, false>, k_finish<3, false, false>,
+       k_finish<4, false, false>},
+      {k_finish<0, false, true>, k_finish<1, false, true>, k_finish<2, false, true>, k_finish<3, false, true>,
+       k_finish<4, false, true>}};
   const int lm = p->dev.lmax < 0 ? 0 : (p->dev.lmax > kMaxL ? kMaxL : p->dev.lmax);
-  GMP_LAUNCH("norm", fns[p->prec == GMP_FP64 ? 1 : 0][lm], dim3((unsigned)blocks), dim3(256), smem, s, p->dev, N,
+  GMP_LAUNCH("norm", fns[mode][lm], dim3((unsigned)blocks), dim3(256), smem, s, p->dev, N,
              partial, chunk_off, order, features, components);
 }
 

@@ -119,8 +119,9 @@ WsLayout carve(const gmp_plan *p, int n_structs, int64_t N, int64_t M, int64_t c
   L.sz = c.take<double>(N);
   L.sid = c.take<int32_t>(N);
   L.ssp = c.take<int32_t>(N);
-  L.cnt = c.take<int32_t>((size_t)NC * p->dev.E * p->dev.S);
+  L.cnt = c.take<int32_t>((size_t)NC * p->dev.E * p->dev.S * p->dev.sub);
   L.ptotal = c.take<int64_t>(NC);
+  L.bucket_max = c.take<int32_t>(NC);
   L.long_q = c.take<int32_t>(NC);
   L.sid_tmp = c.take<int32_t>(N);
   L.scan_aux = c.take<int64_t>(scan_aux_size(scan_n));
@@ -349,6 +350,10 @@ gmp_status gmp_plan_create(const gmp_probe_desc *d, gmp_precision precision, gmp
   P.n_orders = p->n_orders;
   P.order_mask = mask;
   P.kmax = kmax;
+  // The neighbour build orders a bucket's keys by counting, within ranges of
+  // atom indices of a few dozen keys; 256 to 512 counters a centre (l <= 4
+  // plans of 4096 to 60,000 atoms: 166 keys in the buckets of the first shell).
+  P.sub = P.S * P.E <= 48 ? 8 : (P.S * P.E <= 96 ? 4 : (P.S * P.E <= 192 ? 2 : 1));
   const int kb = kmax <= 4 ? 4 : (kmax <= 8 ? 8 : 16);
   P.kb = kb;
   P.lmax = 0;
@@ -718,7 +723,7 @@ static int64_t lds_per_block() {
 // to the long-list kernel, which sorts with the most LDS a workgroup may hold
 // (its static LDS, candidate staging and bucket counters, takes up to
 // kFillStaticLds bytes).
-constexpr int64_t kFillStaticLds = 12 * 1024;
+constexpr int64_t kFillStaticLds = 12 * 1024;  // (and the counters per range of atom indices, up to 2.7 KB)
 constexpr int64_t kShortSortMax = 8192;
 int long_keys_for(const gmp_plan *p) {
   const int nbk = p->dev.E * p->dev.S;

@@ -120,6 +120,7 @@ struct StructInfo {
 // coefficient rows hold -beta (scaled), A_0 = B, A_1..A_4 = 0, -beta.
 struct PlanDev {
   int S, E, n_orders, lmax, order_mask, kmax, kb, nf, ncomp_total;  // kb: primitive stride of the tables (4/8/16)
+  int sub;                           // ranges of atom index per (shell, species) bucket in the neighbour build
   int n_sig, dens_slot, dens_order;  // sigmas, density slot, index of order -1 in orders (-1: none)
   int screen;                        // per-primitive screening (radius^2 in column 7 of the tables, FP32 value)
   int tab_n;                         // tabulated radial factors: intervals per (slot, element) (0: exact)
@@ -370,8 +371,9 @@ struct WsLayout {
   double *fw;             // [3][N]
   double *sx, *sy, *sz;   // bin-sorted wrapped positions
   int32_t *sid, *ssp;     // bin-sorted atom index and species
-  int32_t *cnt;           // [N][S][E] neighbours per bucket (shell, species)
-  int64_t *ptotal;        // [N]
+  int32_t *cnt;           // [N][S][E][sub] neighbours per bucket (shell, species) and range of atom indices
+  int64_t *ptotal;        // [N] pairs per centre
+  int32_t *bucket_max;    // [N] longest bucket per centre
   int32_t *long_q;        // [N] slots whose lists the long-list fill kernel writes
   int32_t *sid_tmp;       // [N] atoms placed in their bins in arrival order (before the in-bin ordering)
   int64_t *scan_aux;      // scan block sums

@@ -366,19 +366,39 @@ struct Shells {
   }
 };
 
+// Range of atom indices (of P.sub equal ones over the structure) that an atom
+// falls into: monotone in the index, so the ranges of a bucket are in order.
+struct SubRange {
+  int64_t first;
+  float scale;
+  int last;
+  __device__ SubRange(const PlanDev &P, const BatchDev &bt, int s) {
+    first = bt.atom_offsets[s];
+    const int64_t n = bt.atom_offsets[s + 1] - first;
+    scale = n > 0 ? (float)P.sub / (float)n : 0.f;
+    last = P.sub - 1;
+  }
+  __device__ int of(int32_t j) const {
+    const int r = (int)((float)(int32_t)(j - first) * scale);
+    return r < last ? r : last;
+  }
+};
+
 // One workgroup per centre (centres in cell-list order): count neighbours
-// per (shell, species) bucket; the wavefronts share the centre's candidates.
+// per (shell, species) bucket and range of atom indices; the wavefronts share
+// the centre's candidates.
 template <int SM>
 __global__ __launch_bounds__(256) void k_count(PlanDev P, BatchDev bt, NbrDev nb, const StructInfo *info,
                                                const double *fw, const int64_t *bin_start,
                                                const double *sx, const double *sy, const double *sz,
                                                const int32_t *sid, const int32_t *ssp, const int32_t *astruct,
-                                               int32_t *cnt, int64_t *ptotal, uint32_t *status) {
+                                               int32_t *cnt, int64_t *ptotal, int32_t *bmax, uint32_t *status) {
   extern __shared__ int32_t lds_cnt[];
   __shared__ CandLds lds_cand[4];
   __shared__ int64_t lds_tot[4];
+  __shared__ int32_t lds_max[4];
   const int w = threadIdx.x / kWave, nw = blockDim.x / kWave, lane = lane_id();
-  const int nbk = P.E * P.S;
+  const int nbk = P.E * P.S * P.sub;
   int32_t *c = lds_cnt;
   const int64_t N = n_total(bt);  // stride of rw
   // list slot k (atoms: cell-list order, each XCD one contiguous range), centre i, index g
@@ -391,6 +411,7 @@ __global__ __launch_bounds__(256) void k_count(PlanDev P, BatchDev bt, NbrDev nb
   Cand C;
   cand_setup(C, info, bt, s, fw, g);
   const Shells<SM> shells(P);
+  const SubRange range(P, bt, s);
   const double rix = nb.rw[g], riy = nb.rw[N + g], riz = nb.rw[2 * N + g];
   for_each_candidate(C, bin_start, P.rcmax2, w, nw, lds_cand[w],
                      [&](int t, const int *n, double shx, double shy, double shz) {
@@ -398,37 +419,48 @@ __global__ __launch_bounds__(256) void k_count(PlanDev P, BatchDev bt, NbrDev nb
                        const double dy = (sy[t] - riy) + shy;
                        const double dz = (sz[t] - riz) + shz;
                        const double q = (dx * dx + dy * dy) + dz * dz;
-                       if (q <= P.rcmax2) atomicAdd(&c[shells.of(q) * P.E + ssp[t]], 1);
+                       if (q <= P.rcmax2)
+                         atomicAdd(&c[(shells.of(q) * P.E + ssp[t]) * P.sub + range.of(sid[t])], 1);
                      });
   __syncthreads();
   int64_t tot = 0;
-  for (int t = threadIdx.x; t < nbk; t += blockDim.x) {
-    cnt[k * nbk + t] = c[t];
-    tot += c[t];
+  int32_t longest = 0;
+  for (int t = threadIdx.x; t < nbk; t += blockDim.x) cnt[k * nbk + t] = c[t];
+  for (int b = threadIdx.x; b < P.E * P.S; b += blockDim.x) {
+    int32_t n = 0;
+    for (int r = 0; r < P.sub; ++r) n += c[b * P.sub + r];
+    tot += n;
+    longest = n > longest ? n : longest;
   }
-  for (int o = 32; o >= 1; o >>= 1) tot += __shfl_xor(tot, o, kWave);
-  if (lane == 0) lds_tot[w] = tot;
+  for (int o = 32; o >= 1; o >>= 1) {
+    tot += __shfl_xor(tot, o, kWave);
+    const int32_t y = __shfl_xor(longest, o, kWave);
+    longest = y > longest ? y : longest;
+  }
+  if (lane == 0) { lds_tot[w] = tot; lds_max[w] = longest; }
   __syncthreads();
   if (threadIdx.x == 0) {
     int64_t all = 0;
-    for (int u = 0; u < nw; ++u) all += lds_tot[u];
+    int32_t m = 0;
+    for (int u = 0; u < nw; ++u) { all += lds_tot[u]; m = lds_max[u] > m ? lds_max[u] : m; }
     ptotal[k] = all;
+    bmax[k] = m;
   }
 }
 
 // Longest list (status word 4) and longest (shell, species) bucket (word 5)
 // of the counted lists, for the synchronous build's sort sizes: a grid-stride
-// maximum with one atomic per workgroup and word.
-__global__ __launch_bounds__(256) void k_list_stats(const int64_t *ptotal, int64_t n_centres, const int32_t *cnt,
-                                                    int64_t n_cnt, uint32_t *status) {
+// maximum over the centres with one atomic per workgroup and word.
+__global__ __launch_bounds__(256) void k_list_stats(const int64_t *ptotal, const int32_t *bucket_max,
+                                                    int64_t n_centres, uint32_t *status) {
   __shared__ int64_t lds_m[2][4];
   const int w = threadIdx.x / kWave, lane = lane_id();
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   int64_t lmax = 0, bmax = 0;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n_centres; t += stride)
+  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n_centres; t += stride) {
     lmax = ptotal[t] > lmax ? ptotal[t] : lmax;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n_cnt; t += stride)
-    bmax = cnt[t] > bmax ? cnt[t] : bmax;
+    bmax = bucket_max[t] > bmax ? bucket_max[t] : bmax;
+  }
   for (int o = 32; o >= 1; o >>= 1) {
     const int64_t a = __shfl_xor(lmax, o, kWave), b = __shfl_xor(bmax, o, kWave);
     lmax = a > lmax ? a : lmax;
@@ -471,40 +503,12 @@ __device__ inline void group4(uint64_t *a, int n, int e0, int e1, int e2, int e3
   if (e3 < n) a[e3] = x3;
 }
 
-// Sort a[0..n) of distinct keys ascending by one wavefront.  Up to 128
-// keys: each lane holds one or two keys, counts the keys below each in one
-// pass of broadcast LDS reads and stores them at those ranks (one pass
-// instead of the 16 synchronised passes of a 128-key network; measured
-// faster up to 128 keys, slower at 256).  Longer: bitonic network whose
-// first merge stage compares mirror pairs, so every comparator is ascending
-// and indices >= n act as +infinity without being touched.
+// Sort a[0..n) of distinct keys ascending by one wavefront: bitonic network
+// whose first merge stage compares mirror pairs, so every comparator is
+// ascending and indices >= n act as +infinity without being touched.
 __device__ void wave_sort(uint64_t *a, int n) {
   const int lane = lane_id();
   if (n <= 1) return;
-  if (n <= kWave) {
-    const uint64_t k = lane < n ? a[lane] : 0ull;
-    int rank = 0;
-    for (int m = 0; m < n; ++m) rank += a[m] < k ? 1 : 0;
-    wave_lds_sync();
-    if (lane < n) a[rank] = k;
-    wave_lds_sync();
-    return;
-  }
-  if (n <= 2 * kWave) {
-    // keys are below ~0 (the top bits hold a shell < 16), so ~0 pads
-    const uint64_t k0 = a[lane], k1 = lane + kWave < n ? a[lane + kWave] : ~0ull;
-    int r0 = 0, r1 = 0;
-    for (int m = 0; m < n; ++m) {
-      const uint64_t x = a[m];
-      r0 += x < k0 ? 1 : 0;
-      r1 += x < k1 ? 1 : 0;
-    }
-    wave_lds_sync();
-    a[r0] = k0;
-    if (lane + kWave < n) a[r1] = k1;
-    wave_lds_sync();
-    return;
-  }
   int lp2 = 1;
   while ((1 << lp2) < n) ++lp2;
   const int half = 1 << (lp2 - 1);
@@ -550,17 +554,38 @@ __device__ void wave_sort(uint64_t *a, int n) {
   }
 }
 
-// Sort key of a pair inside one bucket: (j, n) with the bucket's shell in the
-// top bits (constant within a bucket, so the order is that of (j, n)); the
-// reverse-index search reads the shell from it.
+// Key of a pair: (shell, j, n), the order of a bucket's entries and what the
+// reverse-index search compares.  Atom indices take 27 bits, so the 9 bits
+// below the shell are free: while a list is sorted they hold the species, and
+// the keys of a list then grow from bucket to bucket.
 __device__ inline uint64_t make_key(int64_t j, int n1, int n2, int n3, int shell = 0) {
   return ((uint64_t)shell << 60) | ((uint64_t)j << 24) | ((uint64_t)(n1 + 128) << 16) |
          ((uint64_t)(n2 + 128) << 8) | (uint64_t)(n3 + 128);
 }
+constexpr int kKeySpecies = 54;  // first bit of the species
+constexpr uint64_t kKeySpeciesMask = (uint64_t)(kMaxElements - 1) << kKeySpecies;
+
+// Ranges of up to this many keys are ordered by counting, longer ones by the
+// network of wave_sort (3000 atoms 0.077 ms, 0.072 at 64 and 256; 64 atoms,
+// whose ranges hold 64 to 128 keys, 0.026 ms, 0.035 at 64).
+constexpr int kRankMax = 128;
+// Entries after the keys that read as larger than any key (the counting reads
+// four keys at a time).
+constexpr int kKeyPad = 4;
 
 // Fill of one centre's list by one workgroup: its buckets (shell h,
 // species e), in bucket order h * E + e, in LDS; every bucket sorted by
 // (j, n); j / shift, the bucket starts and the sigma-prefix ends written.
+// The sort: the keys are placed by bucket and range of atom indices as they
+// are found; then every thread takes keys of the list in turn and counts those
+// of its range that are smaller, which gives the entry's place in memory
+// (ranges of different lengths side by side in a wavefront, no barrier and
+// no LDS write; reading past a range's end meets only larger keys).  Long
+// ranges are sorted in place first.  Bound by the enumeration's and the
+// counting's instructions; against a sort of each whole bucket by one
+// wavefront: 4096 atoms, 6.9e6 pairs 0.156 -> 0.096 ms; 60,000 atoms, 1.3e8
+// pairs 2.93 -> 1.93 ms; 512 structures, 3.3e7 pairs 0.745 -> 0.52 ms (the
+// count, which counts by range too, 5% slower: 0.054 -> 0.055 ms).
 // The in-LDS sort holds lds_keys entries.  RANGED = false (the short-list
 // kernel) takes lists that fit in one candidate pass and hands longer ones
 // to the long-list queue; RANGED = true fills range by range of consecutive
@@ -572,42 +597,59 @@ __device__ inline void fill_centre(const PlanDev &P, const BatchDev &bt, const N
                                    const double *sz, const int32_t *sid, const int32_t *ssp, const int32_t *astruct,
                                    const int32_t *cnt, int lds_keys, uint64_t *pair_key, int32_t *pair_centre,
                                    uint64_t *pair_sum, int64_t *abs_bstart, uint32_t *status, int32_t *long_q,
-                                   int64_t k, int64_t i, uint64_t *keys, CandLds *lds_cand, int32_t &lds_bmax) {
+                                   int64_t k, int64_t i, uint64_t *keys, CandLds *lds_cand, int32_t &lds_bmax, int32_t &lds_rmax) {
   const int nbk = P.E * P.S;
-  int32_t *bstart = (int32_t *)(keys + lds_keys);  // [nbk+1]
-  int32_t *cursor = bstart + nbk + 1;              // [nbk]
+  const int sub = P.sub, ns = nbk * sub;
+  int32_t *sstart = (int32_t *)(keys + lds_keys + kKeyPad);  // [ns+1] starts of the ranges of every bucket
+  int32_t *cursor = sstart + ns + 1;                         // [ns]
+  auto bstart = [&](int b) { return sstart[b * sub]; };
   const int64_t g = centre_base(bt) + i;
   const int64_t N = n_total(bt);  // stride of rw
   const int tid = threadIdx.x, w = tid / kWave, nw = blockDim.x / kWave, lane = lane_id();
   const int64_t base = nb.offsets[k];
   const int64_t total = nb.offsets[k + 1] - base;
   const bool overflow = nb.offsets[k + 1] > nb.capacity;
-  if (w == 0) {  // bucket starts: exclusive scan of the centre's bucket counts
-    int32_t carry = 0, vmax = 0;
-    for (int b0 = 0; b0 < nbk; b0 += kWave) {
-      const int b = b0 + lane;
-      const int32_t v = b < nbk ? cnt[k * nbk + b] : 0;
-      vmax = v > vmax ? v : vmax;
-      int32_t incl = v;
-#pragma unroll
-      for (int o = 1; o < kWave; o <<= 1) {
-        const int32_t y = __shfl_up(incl, o, kWave);
-        if (lane >= o) incl += y;
+  for (int t = tid; t < ns; t += blockDim.x) sstart[t] = cnt[k * ns + t];
+  __syncthreads();
+  if (w == 0) {  // starts: exclusive scan of the centre's counts, whole buckets per lane
+    const int per = (nbk + kWave - 1) / kWave;
+    int32_t sum = 0, vmax = 0, rmax = 0;
+    for (int b = lane * per; b < (lane + 1) * per && b < nbk; ++b) {
+      int32_t n = 0;
+      for (int r = 0; r < sub; ++r) {
+        const int32_t v = sstart[b * sub + r];
+        n += v;
+        rmax = v > rmax ? v : rmax;
       }
-      if (b < nbk) bstart[b] = carry + incl - v;
-      carry += __shfl(incl, kWave - 1, kWave);
+      sum += n;
+      vmax = n > vmax ? n : vmax;
+    }
+    int32_t incl = sum;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const int32_t y = __shfl_up(incl, o, kWave);
+      if (lane >= o) incl += y;
+    }
+    int32_t at = incl - sum;
+    for (int t = lane * per * sub; t < (lane + 1) * per * sub && t < ns; ++t) {
+      const int32_t v = sstart[t];
+      sstart[t] = at;
+      at += v;
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
-      const int32_t y = __shfl_xor(vmax, o, kWave);
+      const int32_t y = __shfl_xor(vmax, o, kWave), z = __shfl_xor(rmax, o, kWave);
       vmax = y > vmax ? y : vmax;
+      rmax = z > rmax ? z : rmax;
     }
+    const int32_t all = __shfl(incl, kWave - 1, kWave);
     if (lane == 0) {
-      bstart[nbk] = carry;
+      sstart[ns] = all;
       lds_bmax = vmax;
+      lds_rmax = rmax;
       if (overflow) atomicOr(status, ST_OVERFLOW);
       if (RANGED && vmax > lds_keys) atomicOr(status, ST_SORT_SIZE);
-      if ((int64_t)carry != total) atomicOr(status, ST_INTERNAL);
+      if ((int64_t)all != total) atomicOr(status, ST_INTERNAL);
       // a list the short-list kernel cannot sort in one pass goes to the queue
       if (!RANGED && !overflow && total > lds_keys) long_q[atomicAdd(status + 6, 1u)] = (int32_t)k;
     }
@@ -615,10 +657,10 @@ __device__ inline void fill_centre(const PlanDev &P, const BatchDev &bt, const N
   __syncthreads();
   if (!RANGED && !overflow && total > lds_keys) return;  // the long-list kernel writes this centre
   for (int b = tid; b <= nbk; b += blockDim.x) {
-    nb.bucket_start[k * (nbk + 1) + b] = bstart[b];
-    if (pair_key) abs_bstart[i * (nbk + 1) + b] = base + bstart[b];  // row of the atom: one probe less
+    nb.bucket_start[k * (nbk + 1) + b] = bstart(b);
+    if (pair_key) abs_bstart[i * (nbk + 1) + b] = base + bstart(b);  // row of the atom: one probe less
   }
-  for (int s = tid; s < P.S; s += blockDim.x) nb.sigma_end[k * P.S + s] = bstart[(P.rank_lt[s] + 1) * P.E];
+  for (int s = tid; s < P.S; s += blockDim.x) nb.sigma_end[k * P.S + s] = bstart((P.rank_lt[s] + 1) * P.E);
   if (overflow) return;  // consumers skip centres whose list ends past the capacity
   if (RANGED && lds_bmax > lds_keys) {
     // a bucket does not fit the in-LDS sort: leave in-range placeholder
@@ -644,6 +686,7 @@ __device__ inline void fill_centre(const PlanDev &P, const BatchDev &bt, const N
   Cand C;
   cand_setup(C, info, bt, s, fw, g);
   const Shells<SM> shells(P);
+  const SubRange range(P, bt, s);
   const double rix = nb.rw[g], riy = nb.rw[N + g], riz = nb.rw[2 * N + g];
   // buckets [b_lo, b_hi) whose entries fit the sort together (all of them
   // in the short-list kernel)
@@ -651,11 +694,13 @@ __device__ inline void fill_centre(const PlanDev &P, const BatchDev &bt, const N
     int b_hi = nbk;
     if (RANGED) {
       b_hi = b_lo + 1;
-      while (b_hi < nbk && bstart[b_hi + 1] - bstart[b_lo] <= lds_keys) ++b_hi;
+      while (b_hi < nbk && bstart(b_hi + 1) - bstart(b_lo) <= lds_keys) ++b_hi;
       b_hi = __builtin_amdgcn_readfirstlane(b_hi);  // the same for every thread
     }
-    const int key0 = RANGED ? __builtin_amdgcn_readfirstlane(bstart[b_lo]) : 0;
-    for (int b = b_lo + tid; b < b_hi; b += blockDim.x) cursor[b] = bstart[b] - key0;
+    const int key0 = RANGED ? __builtin_amdgcn_readfirstlane(bstart(b_lo)) : 0;
+    const int n_keys = bstart(b_hi) - key0;
+    for (int t = b_lo * sub + tid; t < b_hi * sub; t += blockDim.x) cursor[t] = sstart[t] - key0;
+    if (tid < kKeyPad) keys[n_keys + tid] = ~0ull;
     __syncthreads();
     for_each_candidate(C, bin_start, P.rcmax2, w, nw, lds_cand[w],
                        [&](int t, const int *n, double shx, double shy, double shz) {
@@ -667,34 +712,51 @@ __device__ inline void fill_centre(const PlanDev &P, const BatchDev &bt, const N
                            const int sh = shells.of(q);
                            const int bk = sh * P.E + ssp[t];
                            if (!RANGED || (bk >= b_lo && bk < b_hi)) {
-                             const int pos = atomicAdd(&cursor[bk], 1);
-                             if (pos < bstart[bk + 1] - key0) keys[pos] = make_key(sid[t], n[0], n[1], n[2], sh);
+                             const int sk = bk * sub + range.of(sid[t]);
+                             const int pos = atomicAdd(&cursor[sk], 1);
+                             if (pos < sstart[sk + 1] - key0)
+                               keys[pos] = make_key(sid[t], n[0], n[1], n[2], sh) | (uint64_t)ssp[t] << kKeySpecies;
                              else atomicOr(status, ST_INTERNAL);
                            }
                          }
                        });
     __syncthreads();
-    for (int b = b_lo + w; b < b_hi; b += nw) {
-      const int b0 = bstart[b], bn = bstart[b + 1] - b0;
-      if (bn == 0) continue;
-      uint64_t *kb = keys + (b0 - key0);
-      wave_sort(kb, bn);
-      const int e = b % P.E;
-      for (int t = lane; t < bn; t += kWave) {
-        uint64_t k = kb[t];
-        int32_t jj = (int32_t)((k >> 24) & 0x7fffffffull);
-        uint32_t n1 = (uint32_t)(((k >> 16) & 0xff) - 128) & 0xffu;
-        uint32_t n2 = (uint32_t)(((k >> 8) & 0xff) - 128) & 0xffu;
-        uint32_t n3 = (uint32_t)((k & 0xff) - 128) & 0xffu;
-        nb.j[base + b0 + t] = jj;
-        nb.shift[base + b0 + t] = (int32_t)(n1 | (n2 << 8) | (n3 << 16) | ((uint32_t)e << 24));
-        if (pair_key) {  // inputs of the reverse-index kernel; the index starts unresolved
-          const int64_t gp = base + b0 + t;
-          pair_key[gp] = k;
-          if ((gp & 15) == 0) pair_sum[gp >> 4] = k;
-          pair_centre[gp] = (int32_t)i;
-          nb.reverse[gp] = -1;
-        }
+    if (lds_rmax > kRankMax) {
+      for (int t = b_lo * sub + w; t < b_hi * sub; t += nw) {
+        const int s0 = sstart[t], n = sstart[t + 1] - s0;
+        if (n > kRankMax) wave_sort(keys + (s0 - key0), n);
+      }
+      __syncthreads();
+    }
+    for (int t = tid; t < n_keys; t += blockDim.x) {
+      const uint64_t key = keys[t];
+      const int e = (int)(key >> kKeySpecies) & (kMaxElements - 1);
+      const int b = (int)(key >> 60) * P.E + e;
+      if (b >= b_hi) { atomicOr(status, ST_INTERNAL); continue; }  // never for lists that were counted alike
+      const int32_t j = (int32_t)((key >> 24) & 0x7ffffffull);
+      const int sk = b * sub + range.of(j);
+      const int b0 = sstart[sk] - key0, b1 = sstart[sk + 1] - key0;
+      int r = t;  // place in the sorted list
+      if (b1 - b0 <= kRankMax) {
+        r = b0;
+        for (int m = b0; m < b1; m += 4)
+          r += ((keys[m] < key ? 1 : 0) + (keys[m + 1] < key ? 1 : 0)) +
+               ((keys[m + 2] < key ? 1 : 0) + (keys[m + 3] < key ? 1 : 0));
+      }
+      if (r >= n_keys) { atomicOr(status, ST_INTERNAL); continue; }
+      const int64_t at = base + key0 + r;
+      const uint32_t n1 = (uint32_t)(((key >> 16) & 0xff) - 128) & 0xffu;
+      const uint32_t n2 = (uint32_t)(((key >> 8) & 0xff) - 128) & 0xffu;
+      const uint32_t n3 = (uint32_t)((key & 0xff) - 128) & 0xffu;
+      nb.j[at] = j;
+      nb.shift[at] = (int32_t)(n1 | (n2 << 8) | (n3 << 16) | ((uint32_t)e << 24));
+      if (pair_key) {  // inputs of the reverse-index kernel; the index starts unresolved
+        const uint64_t k = key & ~kKeySpeciesMask;
+        pair_key[at] = k;
+        if ((at & 15) == 0) pair_sum[at >> 4] = k;
+        const int64_t any = base + key0 + t;
+        pair_centre[any] = (int32_t)i;
+        nb.reverse[any] = -1;
       }
     }
     if (!RANGED) break;
@@ -715,11 +777,12 @@ __global__ __launch_bounds__(256) void k_fill(PlanDev P, BatchDev bt, NbrDev nb,
                                               uint32_t *status, int32_t *long_q) {
   extern __shared__ uint64_t lds_u64[];
   __shared__ CandLds lds_cand[4];
-  __shared__ int32_t lds_bmax;
+  __shared__ int32_t lds_bmax, lds_rmax;
   const int64_t k = xcd_contiguous(blockIdx.x, gridDim.x);  // list slot
   const int64_t i = point_mode(bt) ? k : sid[k];
   fill_centre<false, SM>(P, bt, nb, info, fw, bin_start, sx, sy, sz, sid, ssp, astruct, cnt, lds_keys, pair_key,
-                     pair_centre, pair_sum, abs_bstart, status, long_q, k, i, lds_u64, lds_cand, lds_bmax);
+                     pair_centre, pair_sum, abs_bstart, status, long_q, k, i, lds_u64, lds_cand, lds_bmax,
+                         lds_rmax);
 }
 
 // Long-list fill: persistent workgroups take the queued centres one at a
@@ -735,7 +798,7 @@ __global__ __launch_bounds__(256) void k_fill_long(PlanDev P, BatchDev bt, NbrDe
                                                    uint32_t *status, int32_t *long_q) {
   extern __shared__ uint64_t lds_u64[];
   __shared__ CandLds lds_cand[4];
-  __shared__ int32_t lds_bmax;
+  __shared__ int32_t lds_bmax, lds_rmax;
   __shared__ uint32_t lds_next;
   const uint32_t nq = __atomic_load_n(status + 6, __ATOMIC_RELAXED);
   for (;;) {
@@ -746,7 +809,7 @@ __global__ __launch_bounds__(256) void k_fill_long(PlanDev P, BatchDev bt, NbrDe
     const int64_t k = long_q[q];
     fill_centre<true, SM>(P, bt, nb, info, fw, bin_start, sx, sy, sz, sid, ssp, astruct, cnt, lds_keys, pair_key,
                       pair_centre, pair_sum, abs_bstart, status, long_q, k, point_mode(bt) ? k : sid[k], lds_u64,
-                      lds_cand, lds_bmax);
+                      lds_cand, lds_bmax, lds_rmax);
     __syncthreads();  // lds_next, the keys and the bucket starts are reused
   }
 }
@@ -841,18 +904,17 @@ void launch_scatter(const BatchDev &bt, const NbrDev &nb, const WsLayout &L, int
 void launch_count(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, const WsLayout &L, hipStream_t s) {
   int64_t blocks = n_centres(bt);
   if (blocks == 0) return;
-  size_t smem = sizeof(int32_t) * p->dev.E * p->dev.S;
+  size_t smem = sizeof(int32_t) * p->dev.E * p->dev.S * p->dev.sub;
   auto kern = p->dev.S <= 8 ? k_count<8> : (p->dev.S <= 12 ? k_count<12> : k_count<kMaxSigmas>);
   GMP_LAUNCH("nbr_count", kern, dim3((unsigned)blocks), dim3(256), smem, s, p->dev, bt, nb, L.sinfo, L.fw,
-             L.bin_start, L.sx, L.sy, L.sz, L.sid, L.ssp, L.astruct, L.cnt, L.ptotal, L.status);
+             L.bin_start, L.sx, L.sy, L.sz, L.sid, L.ssp, L.astruct, L.cnt, L.ptotal, L.bucket_max, L.status);
 }
 
 void launch_list_stats(const gmp_plan *p, const BatchDev &bt, const WsLayout &L, hipStream_t s) {
-  const int64_t nc = n_centres(bt), ncnt = nc * p->dev.E * p->dev.S;
-  int64_t blocks = (ncnt + 256 * 16 - 1) / (256 * 16);
-  blocks = blocks < 1 ? 1 : (blocks > 256 ? 256 : blocks);
+  const int64_t nc = n_centres(bt);
+  const int64_t blocks = (nc + 1023) / 1024 > 256 ? 256 : (nc + 1023) / 1024;
   if (nc > 0)
-    GMP_LAUNCH("nbr_list_stats", k_list_stats, dim3((unsigned)blocks), dim3(256), 0, s, L.ptotal, nc, L.cnt, ncnt,
+    GMP_LAUNCH("nbr_list_stats", k_list_stats, dim3((unsigned)blocks), dim3(256), 0, s, L.ptotal, L.bucket_max, nc,
                L.status);
 }
 
@@ -861,13 +923,13 @@ void launch_fill(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, const 
   int nbk = p->dev.E * p->dev.S;
   if (n_centres(bt) == 0) return;
   uint64_t *pk = (nb.reverse && !point_mode(bt)) ? L.pair_key : (uint64_t *)nullptr;
-  size_t smem = sizeof(uint64_t) * lds_keys + sizeof(int32_t) * (2 * nbk + 2);
+  size_t smem = sizeof(uint64_t) * (lds_keys + kKeyPad) + sizeof(int32_t) * (2 * nbk * p->dev.sub + 2);
   auto kern = p->dev.S <= 8 ? k_fill<8> : (p->dev.S <= 12 ? k_fill<12> : k_fill<kMaxSigmas>);
   GMP_LAUNCH("nbr_fill_sort", kern, dim3((unsigned)n_centres(bt)), dim3(256), smem, s, p->dev, bt, nb, L.sinfo,
              L.fw, L.bin_start, L.sx, L.sy, L.sz, L.sid, L.ssp, L.astruct, L.cnt, lds_keys, pk, L.pair_centre,
              L.pair_sum, L.abs_bstart, L.status, L.long_q);
   if (long_keys > 0) {  // one workgroup per CU (its LDS takes most of the CU's), capped by the centre count
-    smem = sizeof(uint64_t) * long_keys + sizeof(int32_t) * (2 * nbk + 2);
+    smem = sizeof(uint64_t) * (long_keys + kKeyPad) + sizeof(int32_t) * (2 * nbk * p->dev.sub + 2);
     const int64_t blocks = n_centres(bt) < 256 ? n_centres(bt) : 256;
     auto kern_long = p->dev.S <= 8 ? k_fill_long<8> : (p->dev.S <= 12 ? k_fill_long<12> : k_fill_long<kMaxSigmas>);
     GMP_LAUNCH("nbr_fill_long", kern_long, dim3((unsigned)blocks), dim3(256), smem, s, p->dev, bt, nb, L.sinfo,

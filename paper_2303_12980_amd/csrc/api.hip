@@ -14,7 +14,7 @@ namespace gmp {
 
 // launchers defined in the kernel translation units
 void launch_struct_setup(const gmp_plan *p, const BatchDev &bt, const WsLayout &L, hipStream_t s);
-void launch_wrap(const BatchDev &bt, const NbrDev &nb, const WsLayout &L, int n_elements, hipStream_t s);
+void launch_wrap(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, const WsLayout &L, hipStream_t s);
 void launch_scatter(const BatchDev &bt, const NbrDev &nb, const WsLayout &L, int n_elements, hipStream_t s);
 void launch_count(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, const WsLayout &L, hipStream_t s);
 void launch_list_stats(const gmp_plan *p, const BatchDev &bt, const WsLayout &L, hipStream_t s);
@@ -134,8 +134,8 @@ WsLayout carve(const gmp_plan *p, int n_structs, int64_t N, int64_t M, int64_t c
   L.vbuf = c.take<char>((size_t)capacity * 4 * tsz);
   L.pair_key = c.take<uint64_t>(M > 0 ? 0 : (size_t)capacity);
   L.pair_centre = c.take<int32_t>(M > 0 ? 0 : (size_t)capacity);
-  L.pair_sum = c.take<uint64_t>(M > 0 ? 0 : (size_t)(capacity / 16 + 1));
-  L.abs_bstart = c.take<int64_t>(M > 0 ? 0 : (size_t)N * (p->dev.E * p->dev.S + 1));
+  L.range_start = c.take<int32_t>(M > 0 ? 0 : (size_t)N * (p->dev.E * p->dev.S * p->dev.sub + 1));
+  L.range_col = c.take<int32_t>(N);
   L.cellpart = c.take<double>((size_t)NC * 9);
   const size_t trn = M > 0 ? (size_t)capacity : 0;
   L.tr_key_in = c.take<uint32_t>(trn);
@@ -761,7 +761,7 @@ gmp_status build_impl(const gmp_plan *p, const gmp_batch *b, gmp_neighbors *n, i
   const int64_t NB = N + b->n_structs;
   fill_zero3(L.status, 64 * sizeof(uint32_t), L.bin_count, NB * sizeof(int32_t), L.bin_fill, NB * sizeof(int32_t), s);
   launch_struct_setup(p, bt, L, s);
-  launch_wrap(bt, nb, L, p->dev.E, s);
+  launch_wrap(p, bt, nb, L, s);
   scan_i32_to_i64(L.bin_count, L.bin_start, NB, L.scan_aux, s);
   launch_scatter(bt, nb, L, p->dev.E, s);
   launch_count(p, bt, nb, L, s);

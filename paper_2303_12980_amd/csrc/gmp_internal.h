@@ -384,8 +384,8 @@ struct WsLayout {
   double4 *rw4;           // [N] AoS copy of the wrapped positions
   uint64_t *pair_key;     // [capacity] packed (j, n) of every pair (reverse search)
   int32_t *pair_centre;   // [capacity] centre of every pair (reverse search)
-  uint64_t *pair_sum;     // [capacity/16 + 1] every 16th packed key (first level of the reverse search)
-  int64_t *abs_bstart;    // [N][S*E+1] bucket starts as global pair indices, a row per atom (reverse search)
+  int32_t *range_start;   // [N][S*E*sub+1] starts of the ranges as pair indices, a row per atom (reverse search)
+  int32_t *range_col;     // [N] species and range of atom indices of an atom: its column in such a row, per shell
   // reference points: pairs sorted by neighbour atom (adjoint gather order)
   uint32_t *tr_key_in, *tr_key_out, *tr_val_in, *tr_val_out;  // [capacity] radix-sort ping-pong buffers
   int32_t *tr_hist;       // [256 * tiles] per-tile digit counts

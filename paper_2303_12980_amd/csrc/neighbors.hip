@@ -107,20 +107,42 @@ __global__ void k_struct_setup(BatchDev bt, StructInfo *info, double rcmax, int 
   info[s] = I;
 }
 
+// Range of atom indices (of P.sub equal ones over the structure) that an atom
+// falls into: monotone in the index, so the ranges of a bucket are in order.
+struct SubRange {
+  int64_t first;
+  float scale;
+  int last;
+  __device__ SubRange(const PlanDev &P, const BatchDev &bt, int s) {
+    first = bt.atom_offsets[s];
+    const int64_t n = bt.atom_offsets[s + 1] - first;
+    scale = n > 0 ? (float)P.sub / (float)n : 0.f;
+    last = P.sub - 1;
+  }
+  __device__ int of(int32_t j) const {
+    const int r = (int)((float)(int32_t)(j - first) * scale);
+    return r < last ? r : last;
+  }
+};
+
 // One thread per index g: atoms (wrapped, binned) and reference points
 // (wrapped only; they are centres, never neighbours).  rw, wrap and fw are
 // over the n_total indices.
 __global__ void k_wrap(BatchDev bt, const StructInfo *info, NbrDev nb, double *fw, int32_t *bin_of,
-                       int32_t *bin_count, int32_t *astruct, int n_elements, uint32_t *status) {
+                       int32_t *bin_count, int32_t *astruct, int32_t *range_col, PlanDev P, uint32_t *status) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t N = n_total(bt);
   if (i >= N) return;
   const bool atom = i < bt.n_atoms;
   if (atom) {
     const int sp = bt.species[i];
-    if (sp < 0 || sp >= n_elements) atomicOr(status, ST_SPECIES);
+    if (sp < 0 || sp >= P.E) atomicOr(status, ST_SPECIES);
   }
   const int s = struct_of_index(bt, i);
+  if (atom) {
+    const int sp = bt.species[i];
+    range_col[i] = (sp < 0 ? 0 : (sp >= P.E ? P.E - 1 : sp)) * P.sub + SubRange(P, bt, s).of((int32_t)i);
+  }
   astruct[i] = s;
   const StructInfo &I = info[s];
   const int64_t k = atom ? i : i - bt.n_atoms;
@@ -366,24 +388,6 @@ struct Shells {
   }
 };
 
-// Range of atom indices (of P.sub equal ones over the structure) that an atom
-// falls into: monotone in the index, so the ranges of a bucket are in order.
-struct SubRange {
-  int64_t first;
-  float scale;
-  int last;
-  __device__ SubRange(const PlanDev &P, const BatchDev &bt, int s) {
-    first = bt.atom_offsets[s];
-    const int64_t n = bt.atom_offsets[s + 1] - first;
-    scale = n > 0 ? (float)P.sub / (float)n : 0.f;
-    last = P.sub - 1;
-  }
-  __device__ int of(int32_t j) const {
-    const int r = (int)((float)(int32_t)(j - first) * scale);
-    return r < last ? r : last;
-  }
-};
-
 // One workgroup per centre (centres in cell-list order): count neighbours
 // per (shell, species) bucket and range of atom indices; the wavefronts share
 // the centre's candidates.
@@ -596,7 +600,7 @@ __device__ inline void fill_centre(const PlanDev &P, const BatchDev &bt, const N
                                    const double *fw, const int64_t *bin_start, const double *sx, const double *sy,
                                    const double *sz, const int32_t *sid, const int32_t *ssp, const int32_t *astruct,
                                    const int32_t *cnt, int lds_keys, uint64_t *pair_key, int32_t *pair_centre,
-                                   uint64_t *pair_sum, int64_t *abs_bstart, uint32_t *status, int32_t *long_q,
+                                   int32_t *range_start, uint32_t *status, int32_t *long_q,
                                    int64_t k, int64_t i, uint64_t *keys, CandLds *lds_cand, int32_t &lds_bmax, int32_t &lds_rmax) {
   const int nbk = P.E * P.S;
   const int sub = P.sub, ns = nbk * sub;
@@ -658,8 +662,9 @@ __device__ inline void fill_centre(const PlanDev &P, const BatchDev &bt, const N
   if (!RANGED && !overflow && total > lds_keys) return;  // the long-list kernel writes this centre
   for (int b = tid; b <= nbk; b += blockDim.x) {
     nb.bucket_start[k * (nbk + 1) + b] = bstart(b);
-    if (pair_key) abs_bstart[i * (nbk + 1) + b] = base + bstart(b);  // row of the atom: one probe less
   }
+  if (pair_key)  // rows by atom; pair indices are below 2^31 where there is a reverse index
+    for (int t = tid; t <= ns; t += blockDim.x) range_start[i * (ns + 1) + t] = (int32_t)(base + sstart[t]);
   for (int s = tid; s < P.S; s += blockDim.x) nb.sigma_end[k * P.S + s] = bstart((P.rank_lt[s] + 1) * P.E);
   if (overflow) return;  // consumers skip centres whose list ends past the capacity
   if (RANGED && lds_bmax > lds_keys) {
@@ -675,7 +680,6 @@ __device__ inline void fill_centre(const PlanDev &P, const BatchDev &bt, const N
       if (pair_key) {
         const uint64_t k = make_key(i, 0, 0, 0);
         pair_key[base + t] = k;
-        if (((base + t) & 15) == 0) pair_sum[(base + t) >> 4] = k;
         pair_centre[base + t] = (int32_t)i;
         nb.reverse[base + t] = -1;
       }
@@ -753,7 +757,6 @@ __device__ inline void fill_centre(const PlanDev &P, const BatchDev &bt, const N
       if (pair_key) {  // inputs of the reverse-index kernel; the index starts unresolved
         const uint64_t k = key & ~kKeySpeciesMask;
         pair_key[at] = k;
-        if ((at & 15) == 0) pair_sum[at >> 4] = k;
         const int64_t any = base + key0 + t;
         pair_centre[any] = (int32_t)i;
         nb.reverse[any] = -1;
@@ -773,7 +776,7 @@ __global__ __launch_bounds__(256) void k_fill(PlanDev P, BatchDev bt, NbrDev nb,
                                               const double *sx, const double *sy, const double *sz,
                                               const int32_t *sid, const int32_t *ssp, const int32_t *astruct,
                                               const int32_t *cnt, int lds_keys, uint64_t *pair_key,
-                                              int32_t *pair_centre, uint64_t *pair_sum, int64_t *abs_bstart,
+                                              int32_t *pair_centre, int32_t *range_start,
                                               uint32_t *status, int32_t *long_q) {
   extern __shared__ uint64_t lds_u64[];
   __shared__ CandLds lds_cand[4];
@@ -781,7 +784,7 @@ __global__ __launch_bounds__(256) void k_fill(PlanDev P, BatchDev bt, NbrDev nb,
   const int64_t k = xcd_contiguous(blockIdx.x, gridDim.x);  // list slot
   const int64_t i = point_mode(bt) ? k : sid[k];
   fill_centre<false, SM>(P, bt, nb, info, fw, bin_start, sx, sy, sz, sid, ssp, astruct, cnt, lds_keys, pair_key,
-                     pair_centre, pair_sum, abs_bstart, status, long_q, k, i, lds_u64, lds_cand, lds_bmax,
+                     pair_centre, range_start, status, long_q, k, i, lds_u64, lds_cand, lds_bmax,
                          lds_rmax);
 }
 
@@ -794,7 +797,7 @@ __global__ __launch_bounds__(256) void k_fill_long(PlanDev P, BatchDev bt, NbrDe
                                                    const double *sx, const double *sy, const double *sz,
                                                    const int32_t *sid, const int32_t *ssp, const int32_t *astruct,
                                                    const int32_t *cnt, int lds_keys, uint64_t *pair_key,
-                                                   int32_t *pair_centre, uint64_t *pair_sum, int64_t *abs_bstart,
+                                                   int32_t *pair_centre, int32_t *range_start,
                                                    uint32_t *status, int32_t *long_q) {
   extern __shared__ uint64_t lds_u64[];
   __shared__ CandLds lds_cand[4];
@@ -808,7 +811,7 @@ __global__ __launch_bounds__(256) void k_fill_long(PlanDev P, BatchDev bt, NbrDe
     if (q >= nq) break;
     const int64_t k = long_q[q];
     fill_centre<true, SM>(P, bt, nb, info, fw, bin_start, sx, sy, sz, sid, ssp, astruct, cnt, lds_keys, pair_key,
-                      pair_centre, pair_sum, abs_bstart, status, long_q, k, point_mode(bt) ? k : sid[k], lds_u64,
+                      pair_centre, range_start, status, long_q, k, point_mode(bt) ? k : sid[k], lds_u64,
                       lds_cand, lds_bmax, lds_rmax);
     __syncthreads();  // lds_next, the keys and the bucket starts are reused
   }
@@ -816,15 +819,18 @@ __global__ __launch_bounds__(256) void k_fill_long(PlanDev P, BatchDev bt, NbrDe
 
 // Reverse index: pair (i, j, n) and its mirror (j, i, -n).  One thread per
 // pair; only the owner of each mirror couple -- i < j, or i == j with n >= 0
-// lexicographically -- searches its mirror among the packed keys of j's
-// bucket (shell, species of i; the mirror has the same q, so the shell
-// stored in the pair's key) and writes both entries.  The search is bound by
-// the cache lines it fetches from lists that do not fit in L2, so it runs on
-// two levels: the fill also stores every 16th key (a 16-key window is one
-// 128-byte line) and the bucket starts as global indices.
+// lexicographically -- searches its mirror among the packed keys of j's list
+// and writes both entries.  The mirror has the same q, hence the same shell:
+// it lies in the range of j's list with that shell, i's species and i's range
+// of atom indices, a few dozen keys whose start the fill stored.  Bound by the
+// chain of dependent loads and the cache lines they fetch.  Bucket starts and
+// every 16th key of a bucket probed first: 4096 atoms, 6.9e6 pairs 0.190 ms,
+// now 0.170; 60,000 atoms, 1.3e8 pairs 4.80 -> 4.17 ms; 192 structures 0.300 ->
+// 0.247 ms.  (Searching the 4-byte neighbour indices instead, no keys stored:
+// 0.246 and 5.2 ms; owners gathered into full wavefronts first: 0.190, 4.3.)
 __global__ __launch_bounds__(256) void k_reverse(PlanDev P, BatchDev bt, NbrDev nb, const uint64_t *pair_key,
-                                                 const int32_t *pair_centre, const uint64_t *pair_sum,
-                                                 const int64_t *abs_bstart, int64_t n_pairs, uint32_t *status) {
+                                                 const int32_t *pair_centre, const int32_t *range_start,
+                                                 const int32_t *range_col, int64_t n_pairs, uint32_t *status) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t N = bt.n_atoms;
   const int64_t total = nb.offsets[N];
@@ -841,25 +847,10 @@ __global__ __launch_bounds__(256) void k_reverse(PlanDev P, BatchDev bt, NbrDev 
   const int n1 = (int)((kp >> 16) & 0xff) - 128, n2 = (int)((kp >> 8) & 0xff) - 128, n3 = (int)(kp & 0xff) - 128;
   const int lex = n1 != 0 ? n1 : (n2 != 0 ? n2 : n3);
   if (!((int64_t)j > i || ((int64_t)j == i && lex >= 0))) return;
-  int ei = bt.species[i];
-  ei = ei < 0 ? 0 : (ei >= P.E ? P.E - 1 : ei);
-  const int b = h * P.E + ei;  // the mirror has the same q, hence the same shell
-  const int64_t *ab = abs_bstart + (int64_t)j * (nbk + 1);  // j's bucket starts (rows by atom)
-  const int64_t A = ab[b], Z = ab[b + 1];  // the bucket as global pair indices
+  // the mirror has the same q, hence the same shell
+  const int32_t *row = range_start + (int64_t)j * (nbk * P.sub + 1) + h * P.E * P.sub + range_col[i];
   const uint64_t key = make_key(i, -n1, -n2, -n3, h);
-  // two levels: the every-16th keys that fall inside the bucket (one or two
-  // cache lines) select a 16-key window (one line), searched in turn
-  int64_t lo = A, hi = Z;
-  if (Z - A > 16) {
-    const int64_t sA = (A + 15) >> 4, sB = (Z - 1) >> 4;
-    int64_t a = sA, c = sB + 1;  // first sampled key above the key sought
-    while (a < c) {
-      const int64_t m = (a + c) >> 1;
-      if (pair_sum[m] <= key) a = m + 1; else c = m;
-    }
-    lo = a == sA ? A : (a - 1) * 16;
-    hi = a * 16 < Z ? a * 16 : Z;
-  }
+  int64_t lo = row[0], hi = row[1];
   int64_t found = -1;
   while (lo < hi) {
     const int64_t mid = (lo + hi) >> 1;
@@ -885,11 +876,11 @@ void launch_struct_setup(const gmp_plan *p, const BatchDev &bt, const WsLayout &
              p->tuning.bin_divisor, L.status);
 }
 
-void launch_wrap(const BatchDev &bt, const NbrDev &nb, const WsLayout &L, int n_elements, hipStream_t s) {
+void launch_wrap(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, const WsLayout &L, hipStream_t s) {
   int64_t blocks = (n_total(bt) + 255) / 256;
   if (blocks == 0) return;
   GMP_LAUNCH("nbr_wrap", k_wrap, dim3((unsigned)blocks), dim3(256), 0, s, bt, L.sinfo, nb, L.fw, L.bin_of,
-             L.bin_count, L.astruct, n_elements, L.status);
+             L.bin_count, L.astruct, L.range_col, p->dev, L.status);
 }
 
 void launch_scatter(const BatchDev &bt, const NbrDev &nb, const WsLayout &L, int n_elements, hipStream_t s) {
@@ -927,14 +918,14 @@ void launch_fill(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, const 
   auto kern = p->dev.S <= 8 ? k_fill<8> : (p->dev.S <= 12 ? k_fill<12> : k_fill<kMaxSigmas>);
   GMP_LAUNCH("nbr_fill_sort", kern, dim3((unsigned)n_centres(bt)), dim3(256), smem, s, p->dev, bt, nb, L.sinfo,
              L.fw, L.bin_start, L.sx, L.sy, L.sz, L.sid, L.ssp, L.astruct, L.cnt, lds_keys, pk, L.pair_centre,
-             L.pair_sum, L.abs_bstart, L.status, L.long_q);
+             L.range_start, L.status, L.long_q);
   if (long_keys > 0) {  // one workgroup per CU (its LDS takes most of the CU's), capped by the centre count
     smem = sizeof(uint64_t) * (long_keys + kKeyPad) + sizeof(int32_t) * (2 * nbk * p->dev.sub + 2);
     const int64_t blocks = n_centres(bt) < 256 ? n_centres(bt) : 256;
     auto kern_long = p->dev.S <= 8 ? k_fill_long<8> : (p->dev.S <= 12 ? k_fill_long<12> : k_fill_long<kMaxSigmas>);
     GMP_LAUNCH("nbr_fill_long", kern_long, dim3((unsigned)blocks), dim3(256), smem, s, p->dev, bt, nb, L.sinfo,
                L.fw, L.bin_start, L.sx, L.sy, L.sz, L.sid, L.ssp, L.astruct, L.cnt, long_keys, pk, L.pair_centre,
-               L.pair_sum, L.abs_bstart, L.status, L.long_q);
+               L.range_start, L.status, L.long_q);
   }
 }
 
@@ -944,7 +935,7 @@ void launch_reverse(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, con
   const int64_t blocks = (n_pairs + 255) / 256;
   if (blocks > 0)
     GMP_LAUNCH("nbr_reverse", k_reverse, dim3((unsigned)blocks), dim3(256), 0, s, p->dev, bt, nb, L.pair_key,
-               L.pair_centre, L.pair_sum, L.abs_bstart, n_pairs, L.status);
+               L.pair_centre, L.range_start, L.range_col, n_pairs, L.status);
 }
 
 }  // namespace gmp

@@ -25,6 +25,7 @@ namespace gmp {
 namespace {
 
 constexpr MonoTable kMT = make_mono_table();
+__device__ constexpr HarmTable kHT = make_harm_table();
 
 template <bool F64> struct Real;
 template <> struct Real<false> { using T = float; };
@@ -38,8 +39,9 @@ __device__ inline double exp_scaled(double a, double q) { return exp(a * q); }
 // (atoms, and reference points) its structure and packed position.  The
 // centre's components are staged in LDS, and where every feature and every
 // (slot, monomial) coefficient comes from is decoded once per workgroup
-// into LDS tables.
-template <int LMAX, bool F64>
+// into LDS tables.  GRAD: the block holds the gradient's coefficients in solid
+// harmonics (grad_block), else the monomial coefficients of the polynomials.
+template <int LMAX, bool F64, bool GRAD>
 __global__ __launch_bounds__(256) void k_bwd_coef(PlanDev P, BatchDev bt, NbrDev nb, const double *components,
                                                   const void *grad_features, void *bcoef, double4 *rw4,
                                                   int32_t *astruct, unsigned long long *counter) {
@@ -52,7 +54,7 @@ __global__ __launch_bounds__(256) void k_bwd_coef(PlanDev P, BatchDev bt, NbrDev
   __shared__ double lds_w[nmono(kMaxL)];
   // block sizes are compile-time constants (the index splits below are then
   // multiplications, not integer divisions)
-  constexpr int NM = nmono(LMAX), NB = coef_block(LMAX);
+  constexpr int NM = nmono(LMAX), NB = GRAD ? grad_block(LMAX) : coef_block(LMAX);
   const int S = P.S, NC = P.ncomp_total, NF = P.nf;
   // decode tables after the four wavefronts' buffers.  Feature t: component
   // offset | weight offset << 12 | length << 20 (bit 31: the density
@@ -157,7 +159,19 @@ __global__ __launch_bounds__(256) void k_bwd_coef(PlanDev P, BatchDev bt, NbrDev
     T *out = (T *)bcoef + (size_t)i * S * NB;
     for (int t = lane; t < S * NB; t += kWave) {
       const int s = t / NB, r = t - s * NB;
-      const double v = r < NM ? M[s * NM + r] : 0.0;
+      double v = 0.0;
+      if constexpr (GRAD) {
+        constexpr int Q0 = 3 * nharm(LMAX - 1);
+        if (r < Q0) {  // derivative along x (0), y (1) or z (2): exponent + 1 times the coefficient one degree up
+          const int k = r / 3, x = r - 3 * k, l = hdeg(k) + 1;
+          const int a = kHT.a[k] + (x == 0), b = kHT.b[k] + (x == 1), c = kHT.c[k] + (x == 2);
+          v = (double)(x == 0 ? a : (x == 1 ? b : c)) * M[s * NM + doff(l) + midx(l, a, b)];
+        } else if (r == Q0) {
+          v = M[s * NM];
+        }
+      } else {
+        v = r < NM ? M[s * NM + r] : 0.0;
+      }
       out[t] = (T)v;
     }
   }
@@ -171,12 +185,12 @@ __global__ __launch_bounds__(256) void k_bwd_coef(PlanDev P, BatchDev bt, NbrDev
 // wavefront-uniformly (the gradient reuses them: one LDS value per monomial).  The loads of pair data (j, shift) run two
 // steps ahead and the gathers of the neighbours' wrapped positions one step
 // ahead.  Dynamic LDS: [coefficient table if staged][4 wavefronts][S * NB].
-template <int LMAX, int KB, bool F64, bool LDS, bool SCREEN>
+template <int LMAX, int KB, bool LDS, bool SCREEN>
 __global__ __launch_bounds__(256) void k_bwd_pairs(PlanDev P, BatchDev bt, NbrDev nb, const double4 *rw4,
                                                    const int32_t *astruct, const void *bcoef_, void *vbuf_, int C,
                                                    int64_t n_items,
                                                    unsigned long long *counter, const void *tab_global) {
-  using T = typename Real<F64>::T;
+  using T = float;
   constexpr int NM = nmono(LMAX);
   constexpr int NB = coef_block(LMAX);
   extern __shared__ __align__(16) double lds_dyn[];
@@ -284,7 +298,7 @@ __global__ __launch_bounds__(256) void k_bwd_pairs(PlanDev P, BatchDev bt, NbrDe
         T cl[LMAX + 1], cp[LMAX + 1];
 #pragma unroll
         for (int l = 0; l <= LMAX; ++l) { cl[l] = (T)0; cp[l] = (T)0; }
-        if constexpr (!SCREEN && !F64) {
+        if constexpr (!SCREEN) {
           // as in the overlap kernel: zero rows past an element's own count,
           // the plan's largest count for every lane, row k+1 read ahead
           const T *row = (LDS ? tabl : tabg) + roff;
@@ -342,8 +356,7 @@ __global__ __launch_bounds__(256) void k_bwd_pairs(PlanDev P, BatchDev bt, NbrDe
           if (!((mask >> l) & 1)) continue;
           // P(d) = sum_m M_m d^m and its gradient from the same coefficients:
           // d/dx of x^a y^b z^c is a x^(a-1) y^b z^c (exponents are constants).
-          // FP32: gradient terms summed per exponent value e, then combined as
-          // sum e g_e (fewer instructions); FP64: each term scaled by its e.
+          // Gradient terms summed per exponent value e, then combined as sum e g_e.
           T Q = (T)0, gx[LMAX + 1], gy[LMAX + 1], gz[LMAX + 1];
 #pragma unroll
           for (int e = 0; e <= LMAX; ++e) { gx[e] = (T)0; gy[e] = (T)0; gz[e] = (T)0; }
@@ -353,21 +366,18 @@ __global__ __launch_bounds__(256) void k_bwd_pairs(PlanDev P, BatchDev bt, NbrDe
             const T Mv = bc[m];
             Q = fma_(Mv, mono[m], Q);
             const int a = kMT.ea[m], b = kMT.eb[m], c = kMT.ec[m];
-            const int ia = F64 ? 1 : a, ib = F64 ? 1 : b, ic = F64 ? 1 : c;  // accumulator index
-            if (a >= 1) gx[ia] = fma_(F64 && a > 1 ? (T)a * Mv : Mv, mono[doff(l - 1) + midx(l - 1, a - 1, b)], gx[ia]);
-            if (b >= 1) gy[ib] = fma_(F64 && b > 1 ? (T)b * Mv : Mv, mono[doff(l - 1) + midx(l - 1, a, b - 1)], gy[ib]);
-            if (c >= 1) gz[ic] = fma_(F64 && c > 1 ? (T)c * Mv : Mv, mono[doff(l - 1) + midx(l - 1, a, b)], gz[ic]);
+            if (a >= 1) gx[a] = fma_(Mv, mono[doff(l - 1) + midx(l - 1, a - 1, b)], gx[a]);
+            if (b >= 1) gy[b] = fma_(Mv, mono[doff(l - 1) + midx(l - 1, a, b - 1)], gy[b]);
+            if (c >= 1) gz[c] = fma_(Mv, mono[doff(l - 1) + midx(l - 1, a, b)], gz[c]);
           }
           A = fma_(cp[l], Q, A);
           if (l >= 1) {
             T sx = gx[1], sy = gy[1], sz = gz[1];
-            if constexpr (!F64) {
 #pragma unroll
-              for (int e = 2; e <= l; ++e) {
-                sx = fma_((T)e, gx[e], sx);
-                sy = fma_((T)e, gy[e], sy);
-                sz = fma_((T)e, gz[e], sz);
-              }
+            for (int e = 2; e <= l; ++e) {
+              sx = fma_((T)e, gx[e], sx);
+              sy = fma_((T)e, gy[e], sy);
+              sz = fma_((T)e, gz[e], sz);
             }
             Bx = fma_(cl[l], sx, Bx);
             By = fma_(cl[l], sy, By);
@@ -385,6 +395,159 @@ __global__ __launch_bounds__(256) void k_bwd_pairs(PlanDev P, BatchDev bt, NbrDe
         dst[1] = (T)(vy * occj);
         dst[2] = (T)(vz * occj);
         dst[3] = (T)0;
+      }
+    }
+    wave_lds_sync();  // every lane is done with this centre's coefficients
+  }
+}
+
+// The FP64 pair kernel: the same work split, in solid harmonics.  grad Q_l comes
+// from 2l-1 coefficients a direction; Q_l itself is (d . grad Q_l) / l (Euler's
+// identity); and since A_{l+1} = A_l beta / lambda with gamma = alpha beta /
+// lambda, the derivatives of the radial factors are c'_l = -alpha c_{l+1}, so
+// only the highest order sums one of its own.  Bound by VALU issue and by the
+// LDS reads of the coefficients, about equal: per pair and slot K exponentials,
+// 8 K and some 90 operations, where sums of both radial factors of every order
+// and the 35 monomials with their derivatives took 11 K and 190: 1500 atoms,
+// 2.5e6 pairs, l <= 4, 8 slots 0.289 -> 0.265 ms (152 registers in place of
+// 194: three wavefronts per SIMD; held to three at launch bounds 0.290).
+template <int LMAX, int KB, bool LDS, bool SCREEN>
+__global__ __launch_bounds__(256, 2) void k_bwd_pairs64(PlanDev P, BatchDev bt, NbrDev nb, const double4 *rw4,
+                                                        const int32_t *astruct, const void *bcoef_, void *vbuf_, int C,
+                                                        int64_t n_items, unsigned long long *counter,
+                                                        const void *tab_global) {
+  constexpr int NG = nharm(LMAX - 1), NB = grad_block(LMAX);  // harmonics of the gradients, coefficients per slot
+  extern __shared__ __align__(16) double lds_dyn[];
+  const int S = P.S, E = P.E;
+  const double *__restrict__ tabg = (const double *)tab_global;
+  double *tabl = lds_dyn;
+  // LDS copy with a 16-byte gap after every (slot, element) block, as in k_bwd_pairs
+  constexpr int BLK = KB * kCoefStride, BLKL = BLK + 2;
+  const int tab_n = LDS ? S * E * BLKL : 0;
+  if (LDS)
+    for (int idx = threadIdx.x; idx < S * E * BLK; idx += blockDim.x) tabl[(idx / BLK) * BLKL + idx % BLK] = tabg[idx];
+  __syncthreads();
+  const int lane = lane_id();
+  double *vbuf = (double *)vbuf_;
+  const int mask = P.order_mask, dens = P.dens_slot, kmx = P.kmax;
+  double *bcoef = tabl + tab_n + (size_t)(threadIdx.x / kWave) * S * NB;
+  for (;;) {
+    const int64_t item = next_item(counter);
+    if (item >= n_items) break;
+    const int64_t k = item / C;  // list slot
+    const int c = (int)(item - k * C);
+    if (nb.offsets[k + 1] > nb.capacity) continue;  // list not written (overflowed no-sync build)
+    const int64_t i = nb.order[k];  // its centre
+    {
+      const double *src = (const double *)bcoef_ + (size_t)i * S * NB;
+      for (int t = lane; t < S * NB; t += kWave) bcoef[t] = src[t];
+      wave_lds_sync();
+    }
+    const int64_t g = centre_base(bt) + i;  // index of the centre (atom, or reference point)
+    const int st = astruct[g];
+    const Cell9 cell = load_cell(bt.cell + 9 * (int64_t)st);
+    const int pbc = bt.pbc[st] & 7;
+    const double4 ri4 = rw4[g];
+    const double rix = ri4.x, riy = ri4.y, riz = ri4.z;
+    const int64_t base = nb.offsets[k];
+    const int cnt = (int)(nb.offsets[k + 1] - base);
+    const int clo = (int)((int64_t)cnt * c / C), chi = (int)((int64_t)cnt * (c + 1) / C);
+    const int end_lane = lane < S ? nb.sigma_end[k * S + lane] : 0;  // lane s <-> slot s
+    // pipeline: (jb, wb, rb) current step, (jc, wc) the step after
+    const int32_t ii = (int32_t)g;  // idle lanes read the centre's own packed position
+    int32_t jb = ii, wb = 0, jc = ii, wc = 0;
+    if (clo + lane < chi) { jb = nb.j[base + clo + lane]; wb = nb.shift[base + clo + lane]; }
+    if (clo + kWave + lane < chi) { jc = nb.j[base + clo + kWave + lane]; wc = nb.shift[base + clo + kWave + lane]; }
+    double4 rb = rw4[jb];
+    for (int p0 = clo; p0 < chi; p0 += kWave) {
+      const int p = p0 + lane;
+      const bool act = p < chi;
+      const int32_t w = wb;
+      const double rjx = rb.x, rjy = rb.y, rjz = rb.z, occj = rb.w;  // w: occupancy of j
+      rb = rw4[jc];
+      wb = wc;
+      jc = ii;
+      wc = 0;
+      if (p + 2 * kWave < chi) { jc = nb.j[base + p + 2 * kWave]; wc = nb.shift[base + p + 2 * kWave]; }
+      double shx = 0.0, shy = 0.0, shz = 0.0;
+      if (pbc) image_shift(cell, shift_n(w, 0), shift_n(w, 1), shift_n(w, 2), shx, shy, shz);
+      const double dx = (rjx - rix) + shx;
+      const double dy = (rjy - riy) + shy;
+      const double dz = (rjz - riz) + shz;
+      const double q = (dx * dx + dy * dy) + dz * dz;
+      const int e = shift_species(w);
+      double Y[NG > 0 ? NG : 1];
+      if constexpr (NG > 0)
+        for_harmonics<LMAX - 1, false>(dx, dy, dz, [&](auto mc, double y) { Y[decltype(mc)::value] = y; });
+      double vx = 0.0, vy = 0.0, vz = 0.0;
+      for (int s = 0; s < S; ++s) {
+        const int ends = __builtin_amdgcn_readlane(end_lane, s);
+        if (!(act && p < ends)) continue;
+        const double *row = LDS ? tabl + s * E * BLKL + __umul24(e, BLKL) : tabg + (size_t)(s * E + e) * BLK;
+        const double *bc = (const double *)__builtin_assume_aligned(bcoef + (size_t)s * NB, 16);
+        double A = 0.0, Bx = 0.0, By = 0.0, Bz = 0.0;
+        // f(k, e_k) for the primitives of the row (rows past an element's own count are zero)
+        auto primitives = [&](auto &&f) {
+#pragma unroll
+          for (int kk = 0; kk < KB; ++kk) {
+            if (kk < kmx) {
+              const double *o = row + kk * kCoefStride;
+              bool use = true;
+              if constexpr (SCREEN) {  // per-primitive screening: the primitive's own radius
+                use = (float)q <= (float)o[7];
+                if (__ballot(use) == 0) continue;
+              }
+              double ek = exp_scaled(o[0], q);
+              if constexpr (SCREEN) ek = use ? ek : 0.0;
+              f(o, ek);
+            }
+          }
+        };
+        if (s == dens) {  // v = 2 rho'(q) W d, rho'(q) = sum_k B (-beta) e_k
+          primitives([&](const double *o, double ek) { A = fma(o[1], o[0] * ek, A); });
+          A *= bc[3 * NG];
+        } else {
+          // c_l = sum_k A e_k, and the derivative of the highest order
+          double cl[LMAX + 1], top = 0.0;
+#pragma unroll
+          for (int l = 0; l <= LMAX; ++l) cl[l] = 0.0;
+          primitives([&](const double *o, double ek) {
+#pragma unroll
+            for (int l = 0; l <= LMAX; ++l) cl[l] = fma(o[1 + l], ek, cl[l]);
+            top = fma(o[1 + LMAX], o[0] * ek, top);
+          });
+          const double alpha = -P.alpha[s];
+          if (mask & 1) A = (LMAX > 0 ? alpha * cl[LMAX > 0 ? 1 : 0] : top) * bc[3 * NG];
+#pragma unroll
+          for (int l = 1; l <= LMAX; ++l) {
+            if (!((mask >> l) & 1)) continue;
+            double gx = 0.0, gy = 0.0, gz = 0.0;
+#pragma unroll
+            for (int m = 0; m < NG; ++m) {
+              if (hdeg(m) != l - 1) continue;
+              gx = fma(bc[3 * m], Y[m], gx);
+              gy = fma(bc[3 * m + 1], Y[m], gy);
+              gz = fma(bc[3 * m + 2], Y[m], gz);
+            }
+            const double D = fma(dz, gz, fma(dy, gy, dx * gx));  // l Q_l
+            const double cp = l < LMAX ? alpha * cl[l < LMAX ? l + 1 : l] : top;
+            A = fma(cp * (1.0 / l), D, A);
+            Bx = fma(cl[l], gx, Bx);
+            By = fma(cl[l], gy, By);
+            Bz = fma(cl[l], gz, Bz);
+          }
+        }
+        const double A2 = A + A;
+        vx += fma(A2, dx, Bx);
+        vy += fma(A2, dy, By);
+        vz += fma(A2, dz, Bz);
+      }
+      if (act) {
+        double *dst = vbuf + (size_t)(base + p) * 4;
+        dst[0] = vx * occj;
+        dst[1] = vy * occj;
+        dst[2] = vz * occj;
+        dst[3] = 0.0;
       }
     }
     wave_lds_sync();  // every lane is done with this centre's coefficients
@@ -562,10 +725,14 @@ using PairsFn = void (*)(PlanDev, BatchDev, NbrDev, const double4 *, const int32
                          int64_t, unsigned long long *, const void *);
 // SCREEN: per-primitive screening (its own instantiation keeps the branch
 // out of the loop of plans without it)
+template <int L, int KB, bool F64, bool LDS, bool SCREEN> PairsFn pair_kernel() {
+  if constexpr (F64) return k_bwd_pairs64<L, KB, LDS, SCREEN>;
+  else return k_bwd_pairs<L, KB, LDS, SCREEN>;
+}
 template <int L, bool F64, bool LDS, bool SCREEN> PairsFn pick_kb(int kb) {
-  if (kb <= 4) return k_bwd_pairs<L, 4, F64, LDS, SCREEN>;
-  if (kb <= 8) return k_bwd_pairs<L, 8, F64, LDS, SCREEN>;
-  return k_bwd_pairs<L, 16, F64, LDS, SCREEN>;
+  if (kb <= 4) return pair_kernel<L, 4, F64, LDS, SCREEN>();
+  if (kb <= 8) return pair_kernel<L, 8, F64, LDS, SCREEN>();
+  return pair_kernel<L, 16, F64, LDS, SCREEN>();
 }
 template <bool F64, bool LDS, bool SCREEN> PairsFn pick_l(int lmax, int kb) {
   switch (lmax) {
@@ -583,7 +750,8 @@ template <bool F64, bool LDS> PairsFn pick_pairs(int lmax, int kb, bool screen) 
 }  // namespace
 
 size_t bwd_coef_elems(const gmp_plan *p, int64_t n_atoms) {
-  return (size_t)n_atoms * p->dev.S * coef_block(p->dev.lmax);
+  const int mono = coef_block(p->dev.lmax), grad = p->prec == GMP_FP64 ? grad_block(p->dev.lmax) : 0;
+  return (size_t)n_atoms * p->dev.S * (mono > grad ? mono : grad);
 }
 
 int persistent_blocks(const void *fn, size_t smem, int blocks_per_cu);
@@ -594,9 +762,10 @@ void transpose_by_neighbour(const NbrDev &nb, int64_t n_centres, int64_t n_atoms
 
 // Per-centre adjoint coefficients (grad_features null: unit upstream
 // gradient, i.e. the coefficients of dF/dd of every feature), and the packed
-// positions and structures of all indices.
+// positions and structures of all indices.  `gradient`: FP64 blocks for the
+// backward's pair kernel.
 void launch_bwd_coef(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, const double *components,
-                     const void *grad_features, const WsLayout &L, hipStream_t s) {
+                     const void *grad_features, const WsLayout &L, bool gradient, hipStream_t s) {
   const int64_t blocks_all = (n_total(bt) + 3) / 4;
   if (blocks_all == 0) return;
   const size_t sm = (size_t)p->dev.S * nmono(p->dev.lmax);
@@ -604,11 +773,15 @@ void launch_bwd_coef(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, co
                 sizeof(int32_t) * ((size_t)p->dev.nf + 2 * sm);  // + the decode tables
   using CoefFn = void (*)(PlanDev, BatchDev, NbrDev, const double *, const void *, void *, double4 *, int32_t *,
                           unsigned long long *);
-  static const CoefFn fns[2][kMaxL + 1] = {
-      {k_bwd_coef<0, false>, k_bwd_coef<1, false>, k_bwd_coef<2, false>, k_bwd_coef<3, false>, k_bwd_coef<4, false>},
-      {k_bwd_coef<0, true>, k_bwd_coef<1, true>, k_bwd_coef<2, true>, k_bwd_coef<3, true>, k_bwd_coef<4, true>}};
+  static const CoefFn fns[3][kMaxL + 1] = {
+      {k_bwd_coef<0, false, false>, k_bwd_coef<1, false, false>, k_bwd_coef<2, false, false>,
+       k_bwd_coef<3, false, false>, k_bwd_coef<4, false, false>},
+      {k_bwd_coef<0, true, false>, k_bwd_coef<1, true, false>, k_bwd_coef<2, true, false>,
+       k_bwd_coef<3, true, false>, k_bwd_coef<4, true, false>},
+      {k_bwd_coef<0, true, true>, k_bwd_coef<1, true, true>, k_bwd_coef<2, true, true>, k_bwd_coef<3, true, true>,
+       k_bwd_coef<4, true, true>}};
   const int lm = p->dev.lmax < 0 ? 0 : (p->dev.lmax > kMaxL ? kMaxL : p->dev.lmax);
-  GMP_LAUNCH("adj_coef", fns[p->prec == GMP_FP64 ? 1 : 0][lm], dim3((unsigned)blocks_all), dim3(256), smem, s,
+  GMP_LAUNCH("adj_coef", fns[p->prec == GMP_FP64 ? (gradient ? 2 : 1) : 0][lm], dim3((unsigned)blocks_all), dim3(256), smem, s,
              p->dev, bt, nb, components, grad_features, L.bcoef, L.rw4, L.astruct, L.counter);
 }
 
@@ -625,12 +798,12 @@ void launch_backward(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, co
   const bool f64 = p->prec == GMP_FP64;
   const int64_t blocks = (N + 3) / 4;
   (void)NT;
-  launch_bwd_coef(p, bt, nb, components, grad_features, L, s);
+  launch_bwd_coef(p, bt, nb, components, grad_features, L, true, s);
   const int64_t n_items = N * (int64_t)C;
   const size_t tab_bytes = (size_t)p->dev.S * p->dev.E * p->dev.kb * kCoefStride * (f64 ? 8 : 4);
   const bool use_lds = tab_bytes <= 48 * 1024;
   const size_t tsm = (use_lds ? tab_bytes + (size_t)p->dev.S * p->dev.E * 16 : 0) +  // table with its gaps
-                     4 * (size_t)p->dev.S * coef_block(p->dev.lmax) * (f64 ? 8 : 4);
+                     4 * (size_t)p->dev.S * (f64 ? grad_block(p->dev.lmax) * 8 : coef_block(p->dev.lmax) * 4);
   const void *tab = f64 ? (const void *)p->dev.coef64 : (const void *)p->dev.coef32;
   const bool scr = p->dev.screen != 0;
   PairsFn fn = f64 ? (use_lds ? pick_pairs<true, true>(p->dev.lmax, p->dev.kb, scr)

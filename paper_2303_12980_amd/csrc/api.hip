@@ -404,6 +404,7 @@ gmp_status gmp_plan_create(const gmp_probe_desc *d, gmp_precision precision, gmp
     const double sg = d->sigmas[s];
     p->sigmas[s] = sg;
     const double alpha = 1.0 / (2.0 * sg * sg);
+    P.alpha[s] = alpha;
     const double best = cutoff2(d, s);
     for (int e = 0; e < p->E; ++e)
       for (int k = d->prim_offsets[e]; k < d->prim_offsets[e + 1]; ++k) {

@@ -104,6 +104,26 @@ __host__ __device__ constexpr int round4(int n) { return (n + 3) & ~3; }
 __host__ __device__ constexpr int coef_m(int lmax) { return round4(nmono(lmax)); }
 __host__ __device__ constexpr int coef_block(int lmax) { return coef_m(lmax); }
 
+// The same for the FP64 pair kernel, in solid harmonics: grad Q_l is harmonic of
+// degree l-1, so entry 3k + x is the coefficient of Y_k (k over degrees 0 to
+// LMAX-1) in the x-th derivative of the order one above Y_k's degree, and the
+// last entry is Q_0.
+__host__ __device__ constexpr int grad_block(int lmax) { return (3 * nharm(lmax - 1) + 2) & ~1; }
+// exponents of the monomial (z exponent 0 or 1) that harmonic k extends
+struct HarmTable {
+  int8_t a[25], b[25], c[25];
+};
+__host__ __device__ constexpr HarmTable make_harm_table() {
+  HarmTable t{};
+  for (int l = 0; l <= kMaxL; ++l)
+    for (int c = 0; c <= 1; ++c)
+      for (int a = l - c; a >= 0; --a) {
+        const int k = l * l + (c == 0 ? l - a : 2 * l - a);
+        t.a[k] = (int8_t)a; t.b[k] = (int8_t)(l - a - c); t.c[k] = (int8_t)c;
+      }
+  return t;
+}
+
 struct StructInfo {
   double b[9];        // reciprocal rows
   double reach[3];    // fractional reach rc_max/h_k (periodic axes)
@@ -134,6 +154,7 @@ struct PlanDev {
   int sig_order[kMaxSigmas];      // slots sorted by rc^2 ascending (stable)
   int rank_lt[kMaxSigmas];        // #{s': rc2[s'] < rc2[s]}
   double rc2[kMaxSigmas];
+  double alpha[kMaxSigmas];       // 1/(2 sigma^2) of every sigma's slot
   double rcmax2;
   const float *coef32;            // [S][E][kb][kCoefStride]: -gamma*log2(e), A_0..A_4, -gamma, r^2 (zero rows past K_e)
   const double *coef64;           // [S][E][kb][kCoefStride]: -gamma, A_0..A_4, -gamma, r^2

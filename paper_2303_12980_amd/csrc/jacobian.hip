@@ -223,14 +223,14 @@ template <bool F64, bool LDS> JacFn pick_jac(int lmax, int kb) {
 }  // namespace
 
 void launch_bwd_coef(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, const double *components,
-                     const void *grad_features, const WsLayout &L, hipStream_t s);
+                     const void *grad_features, const WsLayout &L, bool gradient, hipStream_t s);
 int persistent_blocks(const void *fn, size_t smem, int blocks_per_cu);
 
 void launch_jacobian(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, const double *components, void *jac,
                      int64_t ld, const WsLayout &L, int C, hipStream_t s) {
   const int64_t N = n_centres(bt);
   if (N == 0) return;
-  launch_bwd_coef(p, bt, nb, components, nullptr, L, s);
+  launch_bwd_coef(p, bt, nb, components, nullptr, L, false, s);
   const bool f64 = p->prec == GMP_FP64;
   const int64_t n_items = N * (int64_t)C;
   const size_t tab_bytes = (size_t)p->dev.S * p->dev.E * p->dev.kb * kCoefStride * (f64 ? 8 : 4);

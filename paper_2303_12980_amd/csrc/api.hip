@@ -13,11 +13,9 @@
 namespace gmp {
 
 // launchers defined in the kernel translation units
-void launch_struct_setup(const gmp_plan *p, const BatchDev &bt, const WsLayout &L, hipStream_t s);
-void launch_wrap(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, const WsLayout &L, hipStream_t s);
-void launch_scatter(const BatchDev &bt, const NbrDev &nb, const WsLayout &L, int n_elements, hipStream_t s);
+void launch_cells(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, const WsLayout &L, hipStream_t s);
 void launch_count(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, const WsLayout &L, hipStream_t s);
-void launch_list_stats(const gmp_plan *p, const BatchDev &bt, const WsLayout &L, hipStream_t s);
+void launch_offsets(const BatchDev &bt, const WsLayout &L, int64_t *offsets, bool stats, hipStream_t s);
 void launch_fill(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, const WsLayout &L, int lds_keys,
                  int long_keys, hipStream_t s);
 void launch_reverse(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, const WsLayout &L, int64_t n_pairs,
@@ -34,7 +32,6 @@ size_t bwd_coef_elems(const gmp_plan *p, int64_t n_atoms);
 void launch_backward(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, const double *components,
                      const void *grad_features, double *grad_pos, double *grad_cell, const WsLayout &L, int C,
                      int64_t pairs_bound, hipStream_t s);
-void fill_zero3(void *p0, size_t b0, void *p1, size_t b1, void *p2, size_t b2, hipStream_t s);
 void launch_jacobian(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, const double *components, void *jac,
                      int64_t ld, const WsLayout &L, int C, hipStream_t s);
 
@@ -749,7 +746,7 @@ gmp_status build_impl(const gmp_plan *p, const gmp_batch *b, gmp_neighbors *n, i
   hipStream_t s = (hipStream_t)stream;
   WsLayout L = carve(p, b->n_structs, b->n_atoms, batch_points(b), n->capacity, ws, ws_bytes);
   if (L.bytes > ws_bytes) return set_error(GMP_E_NOMEM, "workspace too small");
-  const int64_t N = b->n_atoms, NC = batch_centres(b);
+  const int64_t NC = batch_centres(b);
   BatchDev bt = to_dev(b);
   NbrDev nb = to_dev(n);
   if (NC == 0) {
@@ -759,19 +756,13 @@ gmp_status build_impl(const gmp_plan *p, const gmp_batch *b, gmp_neighbors *n, i
     if (n_pairs) *n_pairs = 0;
     return GMP_OK;
   }
-  const int64_t NB = N + b->n_structs;
-  fill_zero3(L.status, 64 * sizeof(uint32_t), L.bin_count, NB * sizeof(int32_t), L.bin_fill, NB * sizeof(int32_t), s);
-  launch_struct_setup(p, bt, L, s);
-  launch_wrap(p, bt, nb, L, s);
-  scan_i32_to_i64(L.bin_count, L.bin_start, NB, L.scan_aux, s);
-  launch_scatter(bt, nb, L, p->dev.E, s);
+  launch_cells(p, bt, nb, L, s);
   launch_count(p, bt, nb, L, s);
-  scan_i64(L.ptotal, n->offsets, NC, L.scan_aux, s);
+  launch_offsets(bt, L, n->offsets, n_pairs != nullptr, s);
   int lds_keys, long_keys = long_keys_for(p);
   if (n_pairs) {
     int64_t total = 0;
     uint32_t stw[8];
-    launch_list_stats(p, bt, L, s);
     hipError_t e = hipMemcpyAsync(&total, n->offsets + NC, sizeof(int64_t), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipMemcpyAsync(stw, L.status, sizeof(stw), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);

@@ -32,10 +32,12 @@ __device__ inline double dot3(const double *a, const double *b) { return (a[0] *
 __device__ inline int floordiv(int a, int b) { int q = a / b; return (a % b != 0 && ((a < 0) != (b < 0))) ? q - 1 : q; }
 __device__ inline int pmod(int a, int b) { int r = a % b; return r < 0 ? r + b : r; }
 
-__global__ void k_struct_setup(BatchDev bt, StructInfo *info, double rcmax, int bin_div, uint32_t *status) {
-  int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= bt.n_structs) return;
+// Structure s: reciprocal rows, reach, bins.  Faults of the lattice are kept in
+// it (err) and reported by the next step, so that it can run beside the
+// clearing of the status word.
+__device__ inline void struct_setup(const BatchDev &bt, StructInfo *info, int s, double rcmax, int bin_div) {
   StructInfo I;
+  I.err = 0;
   const int pbc = bt.pbc[s] & 7;
   const int64_t n_s = bt.atom_offsets[s + 1] - bt.atom_offsets[s];
   I.pbc = pbc;
@@ -53,7 +55,7 @@ __global__ void k_struct_setup(BatchDev bt, StructInfo *info, double rcmax, int 
     bool ok = isfinite(V) && V != 0.0;
     for (int k = 0; k < 9; ++k) ok = ok && isfinite(a[k]);
     if (!ok) {
-      atomicOr(status, ST_CELL);
+      I.err |= ST_CELL;
     } else {
       for (int k = 0; k < 3; ++k) { I.b[k] = c23[k] / V; I.b[3 + k] = c31[k] / V; I.b[6 + k] = c12[k] / V; }
       const double ell = rcmax / (double)bin_div;
@@ -67,7 +69,7 @@ __global__ void k_struct_setup(BatchDev bt, StructInfo *info, double rcmax, int 
         I.nb[k] = (int)nbk;
         I.reach[k] = rcmax * inv_h * (1.0 + 1e-12) + 1e-12;
         // image shifts must fit a signed byte
-        if (I.reach[k] + 2.0 > 126.0) atomicOr(status, ST_SHIFT_RANGE);
+        if (I.reach[k] + 2.0 > 126.0) I.err |= ST_SHIFT_RANGE;
       }
       // smallest eigenvalue of the metric G = A A^T (rows of A are the lattice vectors), for a lower
       // bound |n.A|^2 >= lambda_min |n|^2 that lets the cell list skip bin images outside the cutoff
@@ -107,6 +109,16 @@ __global__ void k_struct_setup(BatchDev bt, StructInfo *info, double rcmax, int 
   info[s] = I;
 }
 
+// Clears the status words and the bin counters, and sets up the structures.
+__global__ __launch_bounds__(256) void k_setup(BatchDev bt, StructInfo *info, double rcmax, int bin_div,
+                                               uint32_t *status, int32_t *bin_count, int32_t *bin_fill,
+                                               int64_t n_bins) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < 64) status[i] = 0u;
+  if (i < n_bins) { bin_count[i] = 0; bin_fill[i] = 0; }
+  if (i < bt.n_structs) struct_setup(bt, info, (int)i, rcmax, bin_div);
+}
+
 // Range of atom indices (of P.sub equal ones over the structure) that an atom
 // falls into: monotone in the index, so the ranges of a bucket are in order.
 struct SubRange {
@@ -128,10 +140,11 @@ struct SubRange {
 // One thread per index g: atoms (wrapped, binned) and reference points
 // (wrapped only; they are centres, never neighbours).  rw, wrap and fw are
 // over the n_total indices.
-__global__ void k_wrap(BatchDev bt, const StructInfo *info, NbrDev nb, double *fw, int32_t *bin_of,
-                       int32_t *bin_count, int32_t *astruct, int32_t *range_col, PlanDev P, uint32_t *status) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__device__ inline void wrap_index(const BatchDev &bt, const StructInfo *info, const NbrDev &nb, double *fw,
+                                  int32_t *bin_of, int32_t *bin_count, int32_t *astruct, int32_t *range_col,
+                                  const PlanDev &P, uint32_t *status, int64_t i) {
   const int64_t N = n_total(bt);
+  if (i < bt.n_structs && info[i].err) atomicOr(status, info[i].err);
   if (i >= N) return;
   const bool atom = i < bt.n_atoms;
   if (atom) {
@@ -194,11 +207,16 @@ __global__ void k_wrap(BatchDev bt, const StructInfo *info, NbrDev nb, double *f
   atomicAdd(&bin_count[bin], 1);
 }
 
+__global__ void k_wrap(BatchDev bt, const StructInfo *info, NbrDev nb, double *fw, int32_t *bin_of,
+                       int32_t *bin_count, int32_t *astruct, int32_t *range_col, PlanDev P, uint32_t *status) {
+  wrap_index(bt, info, nb, fw, bin_of, bin_count, astruct, range_col, P, status,
+             (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+}
+
 // Atoms into their bins, in arrival order (the slot within a bin comes
-// from an atomic counter); k_bin_order then orders every bin by atom index.
-__global__ void k_scatter(BatchDev bt, const int32_t *bin_of, const int64_t *bin_start, int32_t *bin_fill,
-                          int32_t *sid_tmp) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// from an atomic counter); bin_order then orders every bin by atom index.
+__device__ inline void scatter_atom(const BatchDev &bt, const int32_t *bin_of, const int64_t *bin_start,
+                                    int32_t *bin_fill, int32_t *sid_tmp, int64_t i) {
   if (i >= bt.n_atoms) return;
   int32_t b = bin_of[i];
   int64_t p = bin_start[b] + atomicAdd(&bin_fill[b], 1);
@@ -210,10 +228,9 @@ __global__ void k_scatter(BatchDev bt, const int32_t *bin_of, const int64_t *bin
 // bin-sorted SoA copies (wrapped positions, atom index, species) are written
 // there, and with atoms as centres the list-slot order follows it.  One
 // thread per arrival slot; the threads of one bin read the same members.
-__global__ void k_bin_order(BatchDev bt, NbrDev nb, const int32_t *bin_of, const int64_t *bin_start,
-                            const int32_t *sid_tmp, double *sx, double *sy, double *sz, int32_t *sid, int32_t *ssp,
-                            int n_elements) {
-  int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__device__ inline void bin_order(const BatchDev &bt, const NbrDev &nb, const int32_t *bin_of, const int64_t *bin_start,
+                                 const int32_t *sid_tmp, double *sx, double *sy, double *sz, int32_t *sid,
+                                 int32_t *ssp, int n_elements, int64_t p) {
   if (p >= bt.n_atoms) return;
   const int64_t N = n_total(bt);  // stride of rw
   const int32_t i = sid_tmp[p];
@@ -232,6 +249,45 @@ __global__ void k_bin_order(BatchDev bt, NbrDev nb, const int32_t *bin_of, const
     nb.order[k] = i;
     nb.slot[i] = (int32_t)k;
   }
+}
+
+__global__ void k_scatter(BatchDev bt, const int32_t *bin_of, const int64_t *bin_start, int32_t *bin_fill,
+                          int32_t *sid_tmp) {
+  scatter_atom(bt, bin_of, bin_start, bin_fill, sid_tmp, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+}
+__global__ void k_bin_order(BatchDev bt, NbrDev nb, const int32_t *bin_of, const int64_t *bin_start,
+                            const int32_t *sid_tmp, double *sx, double *sy, double *sz, int32_t *sid, int32_t *ssp,
+                            int n_elements) {
+  bin_order(bt, nb, bin_of, bin_start, sid_tmp, sx, sy, sz, sid, ssp, n_elements,
+            (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+}
+
+// The whole cell list of a small batch by one workgroup: the steps of k_setup,
+// k_wrap, the bin scan, k_scatter and k_bin_order between barriers, one launch
+// in place of five (their launches, not their work, are the time of a call on
+// tens or hundreds of atoms; with 4096 atoms one CU takes longer than the five).
+constexpr int kSmallAtoms = 1024;
+__global__ __launch_bounds__(kScanThreads) void k_small_cells(PlanDev P, BatchDev bt, NbrDev nb, StructInfo *info,
+                                                              double rcmax, int bin_div, uint32_t *status,
+                                                              int32_t *bin_count, int64_t *bin_start,
+                                                              int32_t *bin_fill, double *fw, int32_t *bin_of,
+                                                              int32_t *astruct, int32_t *range_col, int32_t *sid_tmp,
+                                                              double *sx, double *sy, double *sz, int32_t *sid,
+                                                              int32_t *ssp) {
+  __shared__ int64_t wtot[kScanThreads / kWave];
+  const int t = threadIdx.x;  // at least as many threads as structures, atoms and points, and half the bins
+  const int64_t n_bins = bt.n_atoms + bt.n_structs;
+  if (t < 64) status[t] = 0u;
+  for (int64_t i = t; i < n_bins; i += kScanThreads) { bin_count[i] = 0; bin_fill[i] = 0; }
+  if (t < bt.n_structs) struct_setup(bt, info, t, rcmax, bin_div);
+  __syncthreads();
+  wrap_index(bt, info, nb, fw, bin_of, bin_count, astruct, range_col, P, status, t);
+  __syncthreads();
+  block_scan([&](int64_t i) { return (int64_t)bin_count[i]; }, bin_start, n_bins, wtot);
+  __syncthreads();
+  scatter_atom(bt, bin_of, bin_start, bin_fill, sid_tmp, t);
+  __syncthreads();
+  bin_order(bt, nb, bin_of, bin_start, sid_tmp, sx, sy, sz, sid, ssp, P.E, t);
 }
 
 // Range of virtual bins along axis k for a centre at fractional f.
@@ -455,13 +511,12 @@ __global__ __launch_bounds__(256) void k_count(PlanDev P, BatchDev bt, NbrDev nb
 // Longest list (status word 4) and longest (shell, species) bucket (word 5)
 // of the counted lists, for the synchronous build's sort sizes: a grid-stride
 // maximum over the centres with one atomic per workgroup and word.
-__global__ __launch_bounds__(256) void k_list_stats(const int64_t *ptotal, const int32_t *bucket_max,
-                                                    int64_t n_centres, uint32_t *status) {
-  __shared__ int64_t lds_m[2][4];
+__device__ inline void list_stats(const int64_t *ptotal, const int32_t *bucket_max, int64_t n_centres,
+                                  uint32_t *status, int64_t block, int64_t n_blocks, int64_t (*lds_m)[16]) {
   const int w = threadIdx.x / kWave, lane = lane_id();
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  const int64_t stride = n_blocks * blockDim.x;
   int64_t lmax = 0, bmax = 0;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n_centres; t += stride) {
+  for (int64_t t = block * blockDim.x + threadIdx.x; t < n_centres; t += stride) {
     lmax = ptotal[t] > lmax ? ptotal[t] : lmax;
     bmax = bucket_max[t] > bmax ? bucket_max[t] : bmax;
   }
@@ -477,6 +532,22 @@ __global__ __launch_bounds__(256) void k_list_stats(const int64_t *ptotal, const
     for (int k = 0; k < (int)(blockDim.x / kWave); ++k) m = lds_m[threadIdx.x][k] > m ? lds_m[threadIdx.x][k] : m;
     if (m > 0) atomicMax(status + 4 + threadIdx.x, (uint32_t)(m > 0x7fffffff ? 0x7fffffff : m));
   }
+}
+
+__global__ __launch_bounds__(256) void k_list_stats(const int64_t *ptotal, const int32_t *bucket_max,
+                                                    int64_t n_centres, uint32_t *status) {
+  __shared__ int64_t lds_m[2][16];
+  list_stats(ptotal, bucket_max, n_centres, status, blockIdx.x, gridDim.x, lds_m);
+}
+
+// The list offsets (first workgroup) and the list statistics (the others) of a
+// synchronous build, which do not depend on each other, in one launch.
+__global__ __launch_bounds__(kScanThreads) void k_offsets_stats(const int64_t *ptotal, const int32_t *bucket_max,
+                                                                int64_t *offsets, int64_t n_centres,
+                                                                uint32_t *status) {
+  __shared__ int64_t lds_m[2][16];
+  if (blockIdx.x == 0) block_scan([&](int64_t i) { return ptotal[i]; }, offsets, n_centres, lds_m[0]);
+  else list_stats(ptotal, bucket_max, n_centres, status, blockIdx.x - 1, gridDim.x - 1, lds_m);
 }
 
 __device__ inline void cmpswap(uint64_t *a, int i, int l) {
@@ -869,27 +940,28 @@ __global__ __launch_bounds__(256) void k_reverse(PlanDev P, BatchDev bt, NbrDev 
 }  // namespace
 
 // ------------------------------------------------------------------ host launchers
-void launch_struct_setup(const gmp_plan *p, const BatchDev &bt, const WsLayout &L, hipStream_t s) {
-  int nb = (bt.n_structs + 63) / 64;
-  double rcmax = sqrt(p->dev.rcmax2);
-  GMP_LAUNCH("nbr_struct_setup", k_struct_setup, dim3(nb), dim3(64), 0, s, bt, L.sinfo, rcmax,
-             p->tuning.bin_divisor, L.status);
-}
-
-void launch_wrap(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, const WsLayout &L, hipStream_t s) {
-  int64_t blocks = (n_total(bt) + 255) / 256;
-  if (blocks == 0) return;
-  GMP_LAUNCH("nbr_wrap", k_wrap, dim3((unsigned)blocks), dim3(256), 0, s, bt, L.sinfo, nb, L.fw, L.bin_of,
-             L.bin_count, L.astruct, L.range_col, p->dev, L.status);
-}
-
-void launch_scatter(const BatchDev &bt, const NbrDev &nb, const WsLayout &L, int n_elements, hipStream_t s) {
-  int64_t blocks = (bt.n_atoms + 255) / 256;
-  if (blocks == 0) return;
-  GMP_LAUNCH("nbr_scatter", k_scatter, dim3((unsigned)blocks), dim3(256), 0, s, bt, L.bin_of, L.bin_start,
-             L.bin_fill, L.sid_tmp);
-  GMP_LAUNCH("nbr_bin_order", k_bin_order, dim3((unsigned)blocks), dim3(256), 0, s, bt, nb, L.bin_of, L.bin_start,
-             L.sid_tmp, L.sx, L.sy, L.sz, L.sid, L.ssp, n_elements);
+// Cell list: wrap, bins, bin-sorted atoms.  Small batches in one workgroup.
+void launch_cells(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, const WsLayout &L, hipStream_t s) {
+  const int64_t n = n_total(bt), n_bins = bt.n_atoms + bt.n_structs;
+  const double rcmax = sqrt(p->dev.rcmax2);
+  if (n <= kSmallAtoms && bt.n_structs <= kSmallAtoms) {
+    GMP_LAUNCH("nbr_small_cells", k_small_cells, dim3(1), dim3(kScanThreads), 0, s, p->dev, bt, nb, L.sinfo, rcmax,
+               p->tuning.bin_divisor, L.status, L.bin_count, L.bin_start, L.bin_fill, L.fw, L.bin_of, L.astruct,
+               L.range_col, L.sid_tmp, L.sx, L.sy, L.sz, L.sid, L.ssp);
+    return;
+  }
+  auto blocks_of = [](int64_t items) { return dim3((unsigned)((items + 255) / 256)); };
+  const int64_t wraps = n > bt.n_structs ? n : bt.n_structs;  // a thread per structure reports its faults
+  GMP_LAUNCH("nbr_setup", k_setup, blocks_of(n_bins > 64 ? n_bins : 64), dim3(256), 0, s, bt, L.sinfo, rcmax,
+             p->tuning.bin_divisor, L.status, L.bin_count, L.bin_fill, n_bins);
+  GMP_LAUNCH("nbr_wrap", k_wrap, blocks_of(wraps), dim3(256), 0, s, bt, L.sinfo, nb, L.fw, L.bin_of, L.bin_count,
+             L.astruct, L.range_col, p->dev, L.status);
+  scan_i32_to_i64(L.bin_count, L.bin_start, n_bins, L.scan_aux, s);
+  if (bt.n_atoms == 0) return;
+  GMP_LAUNCH("nbr_scatter", k_scatter, blocks_of(bt.n_atoms), dim3(256), 0, s, bt, L.bin_of, L.bin_start, L.bin_fill,
+             L.sid_tmp);
+  GMP_LAUNCH("nbr_bin_order", k_bin_order, blocks_of(bt.n_atoms), dim3(256), 0, s, bt, nb, L.bin_of, L.bin_start,
+             L.sid_tmp, L.sx, L.sy, L.sz, L.sid, L.ssp, p->dev.E);
 }
 
 void launch_count(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, const WsLayout &L, hipStream_t s) {
@@ -901,12 +973,17 @@ void launch_count(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, const
              L.bin_start, L.sx, L.sy, L.sz, L.sid, L.ssp, L.astruct, L.cnt, L.ptotal, L.bucket_max, L.status);
 }
 
-void launch_list_stats(const gmp_plan *p, const BatchDev &bt, const WsLayout &L, hipStream_t s) {
+// List offsets, and with `stats` the longest list and bucket (status words 4, 5).
+void launch_offsets(const BatchDev &bt, const WsLayout &L, int64_t *offsets, bool stats, hipStream_t s) {
   const int64_t nc = n_centres(bt);
-  const int64_t blocks = (nc + 1023) / 1024 > 256 ? 256 : (nc + 1023) / 1024;
-  if (nc > 0)
-    GMP_LAUNCH("nbr_list_stats", k_list_stats, dim3((unsigned)blocks), dim3(256), 0, s, L.ptotal, L.bucket_max, nc,
-               L.status);
+  if (!stats || nc > kSingleScanMax) scan_i64(L.ptotal, offsets, nc, L.scan_aux, s);
+  if (!stats) return;
+  if (nc <= kSingleScanMax) {
+    GMP_LAUNCH("nbr_offsets", k_offsets_stats, dim3((unsigned)(1 + (nc + 4095) / 4096)), dim3(kScanThreads), 0, s,
+               L.ptotal, L.bucket_max, offsets, nc, L.status);
+  } else {
+    GMP_LAUNCH("nbr_list_stats", k_list_stats, dim3(256), dim3(256), 0, s, L.ptotal, L.bucket_max, nc, L.status);
+  }
 }
 
 void launch_fill(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, const WsLayout &L, int lds_keys,

@@ -59,20 +59,36 @@ __device__ inline double exp_scaled(double a, double q) { return exp(a * q); }
 // work-item counter.
 // Indices g < n_total get their structure and packed position; centres
 // c < n_centres their chunk count.
-__global__ void k_overlap_prep(BatchDev bt, NbrDev nb, int kc, int64_t *nch, double4 *rw4,
-                               int32_t *astruct, unsigned long long *counter) {
+__device__ inline int64_t list_chunks(const NbrDev &nb, int kc, int64_t k) {
+  const int64_t end = nb.offsets[k + 1], cnt = end - nb.offsets[k];
+  // a list that ends past the capacity was not written (overflowed no-sync
+  // build, reported in the status word): no work items, zero moments
+  return end > nb.capacity ? 0 : (kc > 0 && cnt > kc ? (cnt + kc - 1) / kc : 1);
+}
+__device__ inline void prep_index(const BatchDev &bt, const NbrDev &nb, double4 *rw4, int32_t *astruct, int64_t i) {
+  if (i >= n_total(bt)) return;
+  const int st = struct_of_index(bt, i);
+  astruct[i] = st;
+  rw4[i] = wrapped_position(bt, nb, i, st);
+}
+__global__ void k_overlap_prep(BatchDev bt, NbrDev nb, int kc, int64_t *nch, double4 *rw4, int32_t *astruct,
+                               unsigned long long *counter) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i == 0) *counter = 0ull;
-  if (i < n_centres(bt)) {
-    const int64_t cnt = nb.offsets[i + 1] - nb.offsets[i];
-    // a list that ends past the capacity was not written (overflowed no-sync
-    // build, reported in the status word): no work items, zero moments
-    nch[i] = nb.offsets[i + 1] > nb.capacity ? 0 : (kc > 0 && cnt > kc ? (cnt + kc - 1) / kc : 1);
-  }
-  if (i < n_total(bt)) {
-    const int st = struct_of_index(bt, i);
-    astruct[i] = st;
-    rw4[i] = wrapped_position(bt, nb, i, st);
+  if (i < n_centres(bt)) nch[i] = list_chunks(nb, kc, i);
+  prep_index(bt, nb, rw4, astruct, i);
+}
+// The same with the scan of the chunk counts, which needs nothing of the rest,
+// in the first workgroup: one launch where one workgroup can scan them.
+__global__ __launch_bounds__(kScanThreads) void k_overlap_prep_scan(BatchDev bt, NbrDev nb, int kc,
+                                                                    int64_t *chunk_off, double4 *rw4,
+                                                                    int32_t *astruct, unsigned long long *counter) {
+  __shared__ int64_t wtot[kScanThreads / kWave];
+  if (blockIdx.x == 0) {
+    if (threadIdx.x == 0) *counter = 0ull;
+    block_scan([&](int64_t k) { return list_chunks(nb, kc, k); }, chunk_off, n_centres(bt), wtot);
+  } else {
+    prep_index(bt, nb, rw4, astruct, (int64_t)(blockIdx.x - 1) * kScanThreads + threadIdx.x);
   }
 }
 
@@ -767,9 +783,14 @@ void launch_overlap(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, dou
                     int32_t *astruct, int64_t pairs_bound, bool components, hipStream_t s) {
   const int64_t N = n_centres(bt), NT = n_total(bt);  // NT >= N
   const int kc = chunk_size(p);
-  GMP_LAUNCH("overlap_prep", k_overlap_prep, dim3((unsigned)((NT + 255) / 256)), dim3(256), 0, s, bt, nb, kc, nch, rw4,
-             astruct, counter);
-  scan_i64(nch, chunk_off, N, scan_aux, s);
+  if (N <= kSingleScanMax) {
+    GMP_LAUNCH("overlap_prep", k_overlap_prep_scan, dim3((unsigned)(1 + (NT + kScanThreads - 1) / kScanThreads)),
+               dim3(kScanThreads), 0, s, bt, nb, kc, chunk_off, rw4, astruct, counter);
+  } else {
+    GMP_LAUNCH("overlap_prep", k_overlap_prep, dim3((unsigned)((NT + 255) / 256)), dim3(256), 0, s, bt, nb, kc, nch,
+               rw4, astruct, counter);
+    scan_i64(nch, chunk_off, N, scan_aux, s);
+  }
   const int lmax = p->dev.lmax, mode = acc_mode(p, components), slots = pass_slots(mode, lmax);
   const int passes = (p->dev.S + slots - 1) / slots, ng = item_groups(p, N, mode, passes);
   const bool f64 = mode == ACC_F64;

@@ -369,8 +369,8 @@ __device__ inline void for_harmonics(T x, T y, T z, F &&f) {
 
 // Structure of index g (atom or reference point).
 __device__ inline int struct_of_index(const BatchDev &bt, int64_t g) {
-  return g < bt.n_atoms ? struct_of_atom(bt.atom_offsets, bt.n_structs, g)
-                        : struct_of_atom(bt.point_offsets, bt.n_structs, g - bt.n_atoms);
+  if (g < bt.n_atoms) return struct_of_atom(bt.atom_offsets, bt.n_structs, g);
+  return struct_of_atom(bt.point_offsets, bt.n_structs, g - bt.n_atoms);
 }
 
 // Wrapped position Rw_i = R_i - ((m1 a1 + m2 a2) + m3 a3) of index i (atom or
@@ -380,12 +380,17 @@ __device__ inline int struct_of_index(const BatchDev &bt, int64_t g) {
 // atom's occupancy (1 when none is given, and for points).
 __device__ inline double4 wrapped_position(const BatchDev &bt, const NbrDev &nb, int64_t i, int s) {
   const bool atom = i < bt.n_atoms;
-  const int64_t k = atom ? i : i - bt.n_atoms;
-  const double *X = atom ? bt.x : bt.px, *Y = atom ? bt.y : bt.py, *Z = atom ? bt.z : bt.pz;
-  double r[3] = {X[k], Y[k], Z[k]};
+  double r[3];
+  if (atom) {
+    r[0] = bt.x[i]; r[1] = bt.y[i]; r[2] = bt.z[i];
+  } else {
+    const int64_t k = i - bt.n_atoms;
+    r[0] = bt.px[k]; r[1] = bt.py[k]; r[2] = bt.pz[k];
+  }
   if (bt.pbc[s] & 7) {
     const double *a = bt.cell + 9 * (int64_t)s;
     const double m0 = (double)nb.wrap[3 * i], m1 = (double)nb.wrap[3 * i + 1], m2 = (double)nb.wrap[3 * i + 2];
+#pragma unroll
     for (int c = 0; c < 3; ++c) {
       double t = m0 * a[c] + m1 * a[3 + c];
       t = t + m2 * a[6 + c];

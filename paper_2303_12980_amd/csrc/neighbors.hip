@@ -42,7 +42,9 @@ __device__ inline void struct_setup(const BatchDev &bt, StructInfo *info, int s,
   const int64_t n_s = bt.atom_offsets[s + 1] - bt.atom_offsets[s];
   I.pbc = pbc;
   I.bin_base = bt.atom_offsets[s] + s;
+#pragma unroll
   for (int k = 0; k < 9; ++k) I.b[k] = 0.0;
+#pragma unroll
   for (int k = 0; k < 3; ++k) { I.nb[k] = 1; I.reach[k] = 0.0; }
   I.lam_lo = 0.0;
   if (pbc) {
@@ -53,12 +55,15 @@ __device__ inline void struct_setup(const BatchDev &bt, StructInfo *info, int s,
     cross3(a, a + 3, c12);
     double V = dot3(a, c23);
     bool ok = isfinite(V) && V != 0.0;
+#pragma unroll
     for (int k = 0; k < 9; ++k) ok = ok && isfinite(a[k]);
     if (!ok) {
       I.err |= ST_CELL;
     } else {
+#pragma unroll
       for (int k = 0; k < 3; ++k) { I.b[k] = c23[k] / V; I.b[3 + k] = c31[k] / V; I.b[6 + k] = c12[k] / V; }
       const double ell = rcmax / (double)bin_div;
+#pragma unroll
       for (int k = 0; k < 3; ++k) {
         if (!(pbc & (1 << k))) continue;
         double inv_h = sqrt(dot3(I.b + 3 * k, I.b + 3 * k));
@@ -75,7 +80,9 @@ __device__ inline void struct_setup(const BatchDev &bt, StructInfo *info, int s,
       // bound |n.A|^2 >= lambda_min |n|^2 that lets the cell list skip bin images outside the cutoff
       {
         double Gm[3][3];
+#pragma unroll
         for (int r = 0; r < 3; ++r)
+#pragma unroll
           for (int c = 0; c < 3; ++c) Gm[r][c] = dot3(a + 3 * r, a + 3 * c);
         const double p1 = Gm[0][1] * Gm[0][1] + Gm[0][2] * Gm[0][2] + Gm[1][2] * Gm[1][2];
         const double qq = (Gm[0][0] + Gm[1][1] + Gm[2][2]) / 3.0;
@@ -97,14 +104,18 @@ __device__ inline void struct_setup(const BatchDev &bt, StructInfo *info, int s,
       }
       // never more bins than atoms (bin slots per structure are n_s + 1)
       int64_t cap = n_s > 1 ? n_s : 1;
-      while ((int64_t)I.nb[0] * I.nb[1] * I.nb[2] > cap) {
-        int kk = 0;
-        if (I.nb[1] > I.nb[kk]) kk = 1;
-        if (I.nb[2] > I.nb[kk]) kk = 2;
-        I.nb[kk] = I.nb[kk] > 1 ? (I.nb[kk] + 1) / 2 : 1;
+      // (constant indices only: an array indexed at run time would live in scratch memory)
+      int n0 = I.nb[0], n1 = I.nb[1], n2 = I.nb[2];
+      while ((int64_t)n0 * n1 * n2 > cap) {
+        const int m01 = n1 > n0 ? n1 : n0;
+        if (n2 > m01) n2 = n2 > 1 ? (n2 + 1) / 2 : 1;
+        else if (n1 > n0) n1 = n1 > 1 ? (n1 + 1) / 2 : 1;
+        else n0 = n0 > 1 ? (n0 + 1) / 2 : 1;
       }
+      I.nb[0] = n0; I.nb[1] = n1; I.nb[2] = n2;
     }
   }
+#pragma unroll
   for (int k = 0; k < 3; ++k) I.inv_nb[k] = 1.0 / (double)I.nb[k];
   info[s] = I;
 }
@@ -159,8 +170,12 @@ __device__ inline void wrap_index(const BatchDev &bt, const StructInfo *info, co
   astruct[i] = s;
   const StructInfo &I = info[s];
   const int64_t k = atom ? i : i - bt.n_atoms;
-  const double *X = atom ? bt.x : bt.px, *Y = atom ? bt.y : bt.py, *Z = atom ? bt.z : bt.pz;
-  const double R[3] = {X[k], Y[k], Z[k]};
+  // (pointers as values, each with its index: a choice between the members'
+  // addresses would put the batch descriptor in scratch memory)
+  const double *X = bt.x + i, *Y = bt.y + i, *Z = bt.z + i;
+  asm volatile("" : "+v"(X), "+v"(Y), "+v"(Z));
+  if (!atom) { X = bt.px + k; Y = bt.py + k; Z = bt.pz + k; }
+  const double R[3] = {*X, *Y, *Z};
   if (!(isfinite(R[0]) && isfinite(R[1]) && isfinite(R[2]))) atomicOr(status, ST_NONFINITE);
   if (atom && bt.occ && !isfinite(bt.occ[i])) atomicOr(status, ST_NONFINITE);
   int m[3] = {0, 0, 0};
@@ -169,6 +184,7 @@ __device__ inline void wrap_index(const BatchDev &bt, const StructInfo *info, co
   double rwv[3] = {R[0], R[1], R[2]};
   if (I.pbc) {
     const double *a = bt.cell + 9 * (int64_t)s;
+#pragma unroll
     for (int k = 0; k < 3; ++k) {
       if (!(I.pbc & (1 << k))) continue;
       double f = dot3(R, I.b + 3 * k);
@@ -182,6 +198,7 @@ __device__ inline void wrap_index(const BatchDev &bt, const StructInfo *info, co
       if (bk < 0) bk = 0;
       b[k] = bk;
     }
+#pragma unroll
     for (int c = 0; c < 3; ++c) {
       double t = (double)m[0] * a[c] + (double)m[1] * a[3 + c];
       t = t + (double)m[2] * a[6 + c];

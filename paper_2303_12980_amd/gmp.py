@@ -441,6 +441,17 @@ class GMPFunction(torch.autograd.Function):
         return gp[:ctx.batch.n_atoms].t().contiguous(), gc.reshape(-1, 9), None, None, None, None
 
 
+def _stream_beside(*others):
+    """A stream that is none of `others`: torch hands its streams out round
+    robin from a pool of 32, so a new Stream() can be one that is in use."""
+    taken = {s.cuda_stream for s in others}
+    for _ in range(64):
+        s = torch.cuda.Stream()
+        if s.cuda_stream not in taken:
+            return s
+    raise RuntimeError("no free stream in torch's pool")
+
+
 class CapturedStep:
     """Neighbour rebuild (no-sync mode) + forward (+ adjoint) recorded once
     into a HIP graph through torch.cuda.graph and replayed: one host call
@@ -465,8 +476,12 @@ class CapturedStep:
         self.mu = torch.empty((N, plan.n_components), dtype=torch.float64, device=dev)
         self.backward = backward
         self.split = backward and concurrent_reverse and nb.reverse is not None
+        # the fork and join of the reverse search need two streams: the capture
+        # runs on `side`, not on torch's default capture stream, which is one
+        # of the pool and can be the very stream the reverse search got
+        side = _stream_beside(torch.cuda.current_stream())
         if self.split:
-            self.rev_stream = torch.cuda.Stream()
+            self.rev_stream = _stream_beside(torch.cuda.current_stream(), side)
             self.ev_built = torch.cuda.Event()
             self.ev_rev = torch.cuda.Event()
         if backward:
@@ -475,14 +490,13 @@ class CapturedStep:
                 self.G.copy_(G)
             self.gpos = torch.empty(3 * batch.n_total, dtype=torch.float64, device=dev)
             self.gcell = torch.empty(batch.n_structs * 9, dtype=torch.float64, device=dev)
-        side = torch.cuda.Stream()
         side.wait_stream(torch.cuda.current_stream())
         with torch.cuda.stream(side):
             self._run()
         torch.cuda.current_stream().wait_stream(side)
         torch.cuda.synchronize()
         self.graph = torch.cuda.CUDAGraph()
-        with torch.cuda.graph(self.graph):
+        with torch.cuda.graph(self.graph, stream=side):
             self._run()
         # the graph holds raw addresses: keep every buffer it touches alive;
         # the workspace buffer is the one captured (ws.buf may be replaced

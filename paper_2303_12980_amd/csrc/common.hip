@@ -96,8 +96,8 @@ __global__ void k_scan_apply(const Tin *in, int64_t *out, int64_t n, const int64
 // Short arrays: one workgroup.
 template <typename Tin>
 __global__ __launch_bounds__(kScanThreads) void k_scan_single(const Tin *in, int64_t *out, int64_t n) {
-  __shared__ int64_t wtot[kScanThreads / kWave];
-  block_scan([&](int64_t i) { return (int64_t)in[i]; }, out, n, wtot);
+  __shared__ int64_t words[kScanWords];
+  block_scan([&](int64_t i) { return (int64_t)in[i]; }, out, n, words);
 }
 
 template <typename Tin>

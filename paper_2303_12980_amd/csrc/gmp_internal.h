@@ -243,57 +243,10 @@ __device__ inline double wave_sum(double v) {
   return v;
 }
 
-// Exclusive prefix sums of f(0..n-1) by one workgroup of kScanThreads threads,
-// out[n] the total: tiles of four items a thread, wavefronts scanned with
-// shuffles, the wavefront totals by the first wavefront, a running carry.
-constexpr int kScanThreads = 1024;
-template <typename F>
-__device__ inline void block_scan(F &&f, int64_t *out, int64_t n, int64_t *wtot) {
-  const int t = threadIdx.x, lane = lane_id(), w = t / kWave;
-  int64_t carry = 0;
-  for (int64_t base = 0; base < n; base += kScanThreads * 4) {
-    int64_t v[4];
-    int64_t s = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int64_t i = base + (int64_t)t * 4 + k;
-      v[k] = i < n ? (int64_t)f(i) : 0;
-      s += v[k];
-    }
-    int64_t incl = s;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-      const int64_t y = __shfl_up(incl, o, kWave);
-      if (lane >= o) incl += y;
-    }
-    if (lane == kWave - 1) wtot[w] = incl;
-    __syncthreads();
-    if (w == 0) {
-      const int64_t x = lane < kScanThreads / kWave ? wtot[lane] : 0;
-      int64_t xi = x;
-#pragma unroll
-      for (int o = 1; o < kScanThreads / kWave; o <<= 1) {
-        const int64_t y = __shfl_up(xi, o, kWave);
-        if (lane >= o) xi += y;
-      }
-      if (lane < kScanThreads / kWave) wtot[lane] = xi - x;  // exclusive wavefront offsets
-    }
-    __syncthreads();
-    int64_t ex = carry + wtot[w] + (incl - s);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int64_t i = base + (int64_t)t * 4 + k;
-      if (i < n) out[i] = ex;
-      ex += v[k];
-    }
-    // the tile total: last thread's inclusive end
-    if (t == kScanThreads - 1) wtot[0] = ex - carry;
-    __syncthreads();
-    carry += wtot[0];
-    __syncthreads();
-  }
-  if (t == 0) out[n] = carry;
-}
+}  // namespace gmp
+#include "block_scan.h"
+namespace gmp {
+
 constexpr int64_t kSingleScanMax = 65536;  // items one workgroup scans (longer: reduce / scan / apply)
 
 __device__ inline int struct_of_atom(const int64_t *off, int n_structs, int64_t i) {

@@ -291,7 +291,7 @@ __global__ __launch_bounds__(kScanThreads) void k_small_cells(PlanDev P, BatchDe
                                                               int32_t *astruct, int32_t *range_col, int32_t *sid_tmp,
                                                               double *sx, double *sy, double *sz, int32_t *sid,
                                                               int32_t *ssp) {
-  __shared__ int64_t wtot[kScanThreads / kWave];
+  __shared__ int64_t words[kScanWords];
   const int t = threadIdx.x;  // at least as many threads as structures, atoms and points, and half the bins
   const int64_t n_bins = bt.n_atoms + bt.n_structs;
   if (t < 64) status[t] = 0u;
@@ -300,7 +300,7 @@ __global__ __launch_bounds__(kScanThreads) void k_small_cells(PlanDev P, BatchDe
   __syncthreads();
   wrap_index(bt, info, nb, fw, bin_of, bin_count, astruct, range_col, P, status, t);
   __syncthreads();
-  block_scan([&](int64_t i) { return (int64_t)bin_count[i]; }, bin_start, n_bins, wtot);
+  block_scan([&](int64_t i) { return (int64_t)bin_count[i]; }, bin_start, n_bins, words);
   __syncthreads();
   scatter_atom(bt, bin_of, bin_start, bin_fill, sid_tmp, t);
   __syncthreads();
@@ -562,8 +562,8 @@ __global__ __launch_bounds__(256) void k_list_stats(const int64_t *ptotal, const
 __global__ __launch_bounds__(kScanThreads) void k_offsets_stats(const int64_t *ptotal, const int32_t *bucket_max,
                                                                 int64_t *offsets, int64_t n_centres,
                                                                 uint32_t *status) {
-  __shared__ int64_t lds_m[2][16];
-  if (blockIdx.x == 0) block_scan([&](int64_t i) { return ptotal[i]; }, offsets, n_centres, lds_m[0]);
+  __shared__ int64_t words[kScanWords], lds_m[2][16];
+  if (blockIdx.x == 0) block_scan([&](int64_t i) { return ptotal[i]; }, offsets, n_centres, words);
   else list_stats(ptotal, bucket_max, n_centres, status, blockIdx.x - 1, gridDim.x - 1, lds_m);
 }
 

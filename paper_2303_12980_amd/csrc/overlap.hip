@@ -83,10 +83,10 @@ __global__ void k_overlap_prep(BatchDev bt, NbrDev nb, int kc, int64_t *nch, dou
 __global__ __launch_bounds__(kScanThreads) void k_overlap_prep_scan(BatchDev bt, NbrDev nb, int kc,
                                                                     int64_t *chunk_off, double4 *rw4,
                                                                     int32_t *astruct, unsigned long long *counter) {
-  __shared__ int64_t wtot[kScanThreads / kWave];
+  __shared__ int64_t words[kScanWords];
   if (blockIdx.x == 0) {
     if (threadIdx.x == 0) *counter = 0ull;
-    block_scan([&](int64_t k) { return list_chunks(nb, kc, k); }, chunk_off, n_centres(bt), wtot);
+    block_scan([&](int64_t k) { return list_chunks(nb, kc, k); }, chunk_off, n_centres(bt), words);
   } else {
     prep_index(bt, nb, rw4, astruct, (int64_t)(blockIdx.x - 1) * kScanThreads + threadIdx.x);
   }

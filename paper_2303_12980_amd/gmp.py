@@ -452,6 +452,13 @@ def _stream_beside(*others):
     raise RuntimeError("no free stream in torch's pool")
 
 
+def refuse_concurrent_reverse():
+    raise _lib.GMPError(_lib.GMP_E_UNSUPPORTED,
+                        "a captured step with its reverse search on a second stream (concurrent_reverse=True) is "
+                        "switched off: the replay of such steps has ended the host process; capture it without, or "
+                        "run build_reverse on a second stream eagerly")
+
+
 class CapturedStep:
     """Neighbour rebuild (no-sync mode) + forward (+ adjoint) recorded once
     into a HIP graph through torch.cuda.graph and replayed: one host call
@@ -459,15 +466,19 @@ class CapturedStep:
     grad_pos / grad_cell when backward=True); inputs are read from the
     batch's tensors, so updating batch.xyz / batch.cell in place and
     replaying featurizes the new geometry.  `nb` (from a sync build) fixes
-    the capacity; call check_status(ws) to see overflows.  With backward
-    and concurrent_reverse, the reverse-pair search is recorded on a second
-    stream beside the forward and the adjoint waits for it: slower than one
-    stream where the search is short (4096 atoms: 1.08 -> 1.12 ms), faster
-    where it is long and bound by memory latency (100,000 atoms: 56.2 ->
-    52.9 ms); off by default, autotune.autotune times both for a step."""
+    the capacity; call check_status(ws) to see overflows.
+
+    concurrent_reverse (the reverse-pair search recorded on a second stream
+    beside the forward) is refused where it would have an effect: processes
+    that had captured several such steps ended with a segmentation fault of the
+    host inside replay(), and the cause is not known.  Eager steps may run the
+    search on a second stream (build_neighbors with defer_reverse, then
+    build_reverse there)."""
 
     def __init__(self, plan: GMPPlan, batch: DeviceBatch, ws: Workspace, nb: Neighbors, backward=False, G=None,
                  concurrent_reverse=False):
+        if backward and concurrent_reverse and nb.reverse is not None:
+            refuse_concurrent_reverse()
         self.plan, self.batch, self.ws, self.nb = plan, batch, ws, nb
         dev = batch.species.device
         N = batch.n_centres
@@ -475,15 +486,8 @@ class CapturedStep:
         self.F = torch.empty((N, plan.n_features), dtype=plan.dtype, device=dev)
         self.mu = torch.empty((N, plan.n_components), dtype=torch.float64, device=dev)
         self.backward = backward
-        self.split = backward and concurrent_reverse and nb.reverse is not None
-        # the fork and join of the reverse search need two streams: the capture
-        # runs on `side`, not on torch's default capture stream, which is one
-        # of the pool and can be the very stream the reverse search got
+        # never torch's default capture stream: that one is of the same pool as a caller's streams
         side = _stream_beside(torch.cuda.current_stream())
-        if self.split:
-            self.rev_stream = _stream_beside(torch.cuda.current_stream(), side)
-            self.ev_built = torch.cuda.Event()
-            self.ev_rev = torch.cuda.Event()
         if backward:
             self.G = torch.zeros((N, plan.n_features), dtype=plan.dtype, device=dev)
             if G is not None:
@@ -508,18 +512,9 @@ class CapturedStep:
 
     def _run(self):
         L = _lib.load()
-        main = torch.cuda.current_stream()
-        rebuild_neighbors_nosync(self.plan, self.batch, self.ws, self.nb, defer_reverse=self.split)
-        if self.split:
-            self.ev_built.record(main)
-            self.rev_stream.wait_event(self.ev_built)
-            with torch.cuda.stream(self.rev_stream):
-                build_reverse(self.plan, self.batch, self.ws, self.nb)
-            self.ev_rev.record(self.rev_stream)
+        rebuild_neighbors_nosync(self.plan, self.batch, self.ws, self.nb)
         features(self.plan, self.batch, self.nb, self.ws, True, out=self.F, comp_out=self.mu)
         if self.backward:
-            if self.split:
-                main.wait_event(self.ev_rev)
             buf = self.ws.buf
             bd, nd = self.batch.desc(), self.nb.desc()
             check(L.gmp_features_backward(self.plan.handle, ctypes.byref(bd), ctypes.byref(nd), _ptr(self.mu),

@@ -145,12 +145,14 @@ def other_workloads_apart():
     """other_workloads in a process of its own: in one process with all the
     parts before it, the replay of a captured step of the 512-structure
     workload has ended in a segmentation fault on the host whose cause is not
-    known; alone it runs.  A child that fails is reported in the output."""
+    known; alone it runs.  Returns its line and its exit status (a child that
+    fails is named in the line, and the benchmark ends with its status)."""
     r = subprocess.run([sys.executable, os.path.abspath(__file__), "--others-only"], stdout=subprocess.PIPE, text=True)
-    if r.returncode != 0:
+    lines = r.stdout.strip().splitlines()
+    if r.returncode != 0 or not lines:
         print(f"[bench] the other workloads ended with status {r.returncode}", file=sys.stderr, flush=True)
-        return {"error": f"exit status {r.returncode}"}
-    return json.loads(r.stdout.strip().splitlines()[-1])
+        return {"error": f"exit status {r.returncode}"}, r.returncode if 0 < r.returncode < 256 else 1
+    return json.loads(lines[-1]), 0
 
 
 def density_variant(g, gs, torch, batch, probes, db, steps=10, warmup=3):
@@ -780,9 +782,11 @@ def main():
         del graphs, plan32, nb32, step32
         torch.cuda.empty_cache()
         out["batched"] = batched_vs_per_structure(g, gs, torch)
+    status = 0
     if not args.no_others:
-        out["other_workloads"] = other_workloads_apart()
-    print(json.dumps(out))
+        out["other_workloads"], status = other_workloads_apart()
+    print(json.dumps(out), flush=True)
+    sys.exit(status)
 
 
 if __name__ == "__main__":

@@ -18,6 +18,7 @@
 // each of which is real bin V mod nb with image shift floor(V / nb).  Atoms
 // are stored bin-sorted in SoA arrays so a bin is read with coalesced loads.
 #include "gmp_internal.h"
+#include "pair_key.h"
 
 namespace gmp {
 namespace {
@@ -646,17 +647,6 @@ __device__ void wave_sort(uint64_t *a, int n) {
   }
 }
 
-// Key of a pair: (shell, j, n), the order of a bucket's entries and what the
-// reverse-index search compares.  Atom indices take 27 bits, so the 9 bits
-// below the shell are free: while a list is sorted they hold the species, and
-// the keys of a list then grow from bucket to bucket.
-__device__ inline uint64_t make_key(int64_t j, int n1, int n2, int n3, int shell = 0) {
-  return ((uint64_t)shell << 60) | ((uint64_t)j << 24) | ((uint64_t)(n1 + 128) << 16) |
-         ((uint64_t)(n2 + 128) << 8) | (uint64_t)(n3 + 128);
-}
-constexpr int kKeySpecies = 54;  // first bit of the species
-constexpr uint64_t kKeySpeciesMask = (uint64_t)(kMaxElements - 1) << kKeySpecies;
-
 // Ranges of up to this many keys are ordered by counting, longer ones by the
 // network of wave_sort (3000 atoms 0.077 ms, 0.072 at 64 and 256; 64 atoms,
 // whose ranges hold 64 to 128 keys, 0.026 ms, 0.035 at 64).
@@ -780,6 +770,7 @@ __device__ inline void fill_centre(const PlanDev &P, const BatchDev &bt, const N
   const Shells<SM> shells(P);
   const SubRange range(P, bt, s);
   const double rix = nb.rw[g], riy = nb.rw[N + g], riz = nb.rw[2 * N + g];
+  const int species_mask = bt.n_atoms <= kKeySpeciesAtoms ? kMaxElements - 1 : 0;
   // buckets [b_lo, b_hi) whose entries fit the sort together (all of them
   // in the short-list kernel)
   for (int b_lo = 0; b_lo < nbk;) {
@@ -807,7 +798,8 @@ __device__ inline void fill_centre(const PlanDev &P, const BatchDev &bt, const N
                              const int sk = bk * sub + range.of(sid[t]);
                              const int pos = atomicAdd(&cursor[sk], 1);
                              if (pos < sstart[sk + 1] - key0)
-                               keys[pos] = make_key(sid[t], n[0], n[1], n[2], sh) | (uint64_t)ssp[t] << kKeySpecies;
+                               keys[pos] = make_key(sid[t], n[0], n[1], n[2], sh) |
+                                           (uint64_t)(ssp[t] & species_mask) << kKeySpecies;
                              else atomicOr(status, ST_INTERNAL);
                            }
                          }
@@ -820,35 +812,52 @@ __device__ inline void fill_centre(const PlanDev &P, const BatchDev &bt, const N
       }
       __syncthreads();
     }
-    for (int t = tid; t < n_keys; t += blockDim.x) {
+    auto place = [&](int t, auto species) {
+      constexpr bool SPECIES = decltype(species)::value;
       const uint64_t key = keys[t];
-      const int e = (int)(key >> kKeySpecies) & (kMaxElements - 1);
-      const int b = (int)(key >> 60) * P.E + e;
-      if (b >= b_hi) { atomicOr(status, ST_INTERNAL); continue; }  // never for lists that were counted alike
-      const int32_t j = (int32_t)((key >> 24) & 0x7ffffffull);
+      int32_t j;
+      int e;
+      if constexpr (SPECIES) {
+        j = (int32_t)key_atom_below_species(key);
+        e = key_species(key);
+      } else {
+        j = (int32_t)key_atom(key);
+        e = bt.species[j < bt.n_atoms ? j : 0];
+        e = e < 0 ? 0 : (e >= P.E ? P.E - 1 : e);
+      }
+      const int b = key_shell(key) * P.E + e;
+      if (b >= b_hi) { atomicOr(status, ST_INTERNAL); return; }  // never for lists that were counted alike
       const int sk = b * sub + range.of(j);
       const int b0 = sstart[sk] - key0, b1 = sstart[sk + 1] - key0;
       int r = t;  // place in the sorted list
       if (b1 - b0 <= kRankMax) {
         r = b0;
-        for (int m = b0; m < b1; m += 4)
-          r += ((keys[m] < key ? 1 : 0) + (keys[m + 1] < key ? 1 : 0)) +
-               ((keys[m + 2] < key ? 1 : 0) + (keys[m + 3] < key ? 1 : 0));
+        if constexpr (SPECIES) {
+          for (int m = b0; m < b1; m += 4)
+            r += ((keys[m] < key ? 1 : 0) + (keys[m + 1] < key ? 1 : 0)) +
+                 ((keys[m + 2] < key ? 1 : 0) + (keys[m + 3] < key ? 1 : 0));
+        } else {
+          for (int m = b0; m < b1; ++m) r += keys[m] < key ? 1 : 0;
+        }
       }
-      if (r >= n_keys) { atomicOr(status, ST_INTERNAL); continue; }
+      if (r >= n_keys) { atomicOr(status, ST_INTERNAL); return; }
       const int64_t at = base + key0 + r;
-      const uint32_t n1 = (uint32_t)(((key >> 16) & 0xff) - 128) & 0xffu;
-      const uint32_t n2 = (uint32_t)(((key >> 8) & 0xff) - 128) & 0xffu;
-      const uint32_t n3 = (uint32_t)((key & 0xff) - 128) & 0xffu;
+      const uint32_t n1 = (uint32_t)key_shift(key, 0) & 0xffu;
+      const uint32_t n2 = (uint32_t)key_shift(key, 1) & 0xffu;
+      const uint32_t n3 = (uint32_t)key_shift(key, 2) & 0xffu;
       nb.j[at] = j;
       nb.shift[at] = (int32_t)(n1 | (n2 << 8) | (n3 << 16) | ((uint32_t)e << 24));
       if (pair_key) {  // inputs of the reverse-index kernel; the index starts unresolved
-        const uint64_t k = key & ~kKeySpeciesMask;
-        pair_key[at] = k;
+        pair_key[at] = SPECIES ? key & ~kKeySpeciesMask : key;
         const int64_t any = base + key0 + t;
         pair_centre[any] = (int32_t)i;
         nb.reverse[any] = -1;
       }
+    };
+    if (species_mask) {
+      for (int t = tid; t < n_keys; t += blockDim.x) place(t, std::true_type{});
+    } else {
+      for (int t = tid; t < n_keys; t += blockDim.x) place(t, std::false_type{});
     }
     if (!RANGED) break;
     __syncthreads();  // the next range reuses the keys and cursors
@@ -926,13 +935,13 @@ __global__ __launch_bounds__(256) void k_reverse(PlanDev P, BatchDev bt, NbrDev 
   const int nbk = P.E * P.S;
   const uint64_t kp = pair_key[p];
   const int64_t i = pair_centre[p];
-  const int32_t j = (int32_t)((kp >> 24) & 0x7fffffffull);
-  const int h = (int)(kp >> 60);
+  const int32_t j = (int32_t)key_atom(kp);
+  const int h = key_shell(kp);
   if (i < 0 || i >= N || (int64_t)j >= N || h >= P.S) {  // never for lists the fill wrote
     atomicOr(status, ST_INTERNAL);
     return;
   }
-  const int n1 = (int)((kp >> 16) & 0xff) - 128, n2 = (int)((kp >> 8) & 0xff) - 128, n3 = (int)(kp & 0xff) - 128;
+  const int n1 = key_shift(kp, 0), n2 = key_shift(kp, 1), n3 = key_shift(kp, 2);
   const int lex = n1 != 0 ? n1 : (n2 != 0 ? n2 : n3);
   if (!((int64_t)j > i || ((int64_t)j == i && lex >= 0))) return;
   // the mirror has the same q, hence the same shell

@@ -223,10 +223,6 @@ __device__ inline void radial_from_table(const PlanDev &P, int s, int e, float q
   }
 }
 
-// Squared distance that takes a lane out of a radial sum: far past any
-// cutoff, its exponentials are exact zeros.
-constexpr double kFarQ = 1e30;
-
 // Radial sums c_l += sum_k A_{l,k} exp(-gamma_k q) of NU slots together (NU
 // independent chains per lane).  Table rows past an element's own primitive
 // count are zero (they add exact zeros), so every lane runs the plan's
@@ -234,7 +230,7 @@ constexpr double kFarQ = 1e30;
 // before the rows k are used (the empty asm statement keeps the compiler from
 // sinking the reads).
 template <int LMAX, int KB, int NU>
-__device__ inline void radial_sums(const float *const (&row)[NU], const float (&q)[NU], int kmax,
+__device__ inline void radial_sums(const float *const (&row)[NU], float q, int kmax,
                                    float (&cl)[NU][LMAX + 1]) {
   float4 ra[NU];
   float2 rb[NU];
@@ -252,7 +248,7 @@ __device__ inline void radial_sums(const float *const (&row)[NU], const float (&
     asm volatile("" ::: "memory");
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
-      const float ek = exp_scaled(ra[u].x, q[u]);
+      const float ek = exp_scaled(ra[u].x, q);
       const float av[5] = {ra[u].y, ra[u].z, ra[u].w, rb[u].x, rb[u].y};
 #pragma unroll
       for (int l = 0; l <= LMAX; ++l) cl[u][l] = fma_(av[l], ek, cl[u][l]);
@@ -272,13 +268,13 @@ __device__ inline void radial_sums(const float *const (&row)[NU], const float (&
   }
 }
 template <int LMAX, int KB, int NU>
-__device__ inline void radial_sums(const double *const (&row)[NU], const double (&q)[NU], int kmax,
+__device__ inline void radial_sums(const double *const (&row)[NU], double q, int kmax,
                                    double (&cl)[NU][LMAX + 1]) {
   for (int k = 0; k < kmax; ++k) {
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
       const double *o = row[u] + k * kCoefStride;
-      const double ek = exp_scaled(o[0], q[u]);
+      const double ek = exp_scaled(o[0], q);
 #pragma unroll
       for (int l = 0; l <= LMAX; ++l) cl[u][l] = fma_(o[1 + l], ek, cl[u][l]);
     }
@@ -434,15 +430,23 @@ __global__ __launch_bounds__(256, pass_slots(MODE, LMAX) == 1 ? 3 : 2) void k_ov
         const int tl = ta * NS;
         if (NS > 1 && !SCREEN && !TAB && tl + NS <= S && pa < slot_end(tl)) {  // every slot takes pairs of this step
           const TR *row[NS];
-          TR qu[NS];
 #pragma unroll
           for (int u = 0; u < NS; ++u) {
             row[u] = table_row(__builtin_amdgcn_readlane(so_lane, tl + u), e);
-            qu[u] = p < slot_end(tl + u) ? qv : (TR)kFarQ;
 #pragma unroll
             for (int l = 0; l <= LMAX; ++l) cl[u][l] = (TR)0;
           }
-          radial_sums<LMAX, KB, NS>(row, qu, P.kmax, cl);
+          radial_sums<LMAX, KB, NS>(row, qv, P.kmax, cl);
+          // nothing from the lanes past a slot's prefix: a step in which any
+          // prefix of the pass ends is one in which the shortest does
+          if (slot_end(tl) - pa < kWave) {
+#pragma unroll
+            for (int u = 0; u < NS; ++u) {
+              const bool in = p < slot_end(tl + u);
+#pragma unroll
+              for (int l = 0; l <= LMAX; ++l) cl[u][l] = in ? cl[u][l] : (TR)0;
+            }
+          }
         } else {
           auto slot_radial = [&](auto uc) {
             constexpr int u = decltype(uc)::value;
@@ -469,11 +473,10 @@ __global__ __launch_bounds__(256, pass_slots(MODE, LMAX) == 1 ? 3 : 2) void k_ov
                   }
                 }
               } else {
-                const TR qu[1] = {qv};
                 TR c1[1][LMAX + 1];
 #pragma unroll
                 for (int l = 0; l <= LMAX; ++l) c1[0][l] = (TR)0;
-                radial_sums<LMAX, KB, 1>(row, qu, P.kmax, c1);
+                radial_sums<LMAX, KB, 1>(row, qv, P.kmax, c1);
 #pragma unroll
                 for (int l = 0; l <= LMAX; ++l) cl[u][l] = c1[0][l];
               }
@@ -805,9 +808,10 @@ void launch_overlap(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, dou
                  : f64     ? pick_overlap<ACC_F64>(lmax, kb, use_lds, screen, occ)
                  : mode == ACC_TERMS ? pick_overlap<ACC_TERMS>(lmax, kb, use_lds, screen, occ)
                                      : pick_overlap<ACC_WIDE>(lmax, kb, use_lds, screen, occ);
-  const int64_t items_bound = chunks_bound(p, N, pairs_bound) * ng;
   int64_t blocks = persistent_blocks((const void *)fn, smem, p->tuning.blocks_per_cu);
-  const int64_t need = (items_bound + 3) / 4;
+  // no more wavefronts than items: with some idle, those with an item would sit unevenly on the SIMDs
+  const int64_t whole = kc > 0 ? pairs_bound / kc : 0;
+  const int64_t need = ((N > whole ? N : whole) * ng + 3) / 4;
   if (blocks > need) blocks = need;
   if (blocks < 1) blocks = 1;
   // Items per request to the counter: requests from all wavefronts to one

@@ -411,13 +411,14 @@ __global__ __launch_bounds__(256) void k_bwd_pairs(PlanDev P, BatchDev bt, NbrDe
 // and the 35 monomials with their derivatives took 11 K and 190: 1500 atoms,
 // 2.5e6 pairs, l <= 4, 8 slots 0.289 -> 0.265 ms (152 registers in place of
 // 194: three wavefronts per SIMD; held to three at launch bounds 0.290).
-template <int LMAX, int KB, bool LDS, bool SCREEN>
+template <int LMAX, int KB, bool LDS, bool SCREEN, bool STEP_K>
 __global__ __launch_bounds__(256, 2) void k_bwd_pairs64(PlanDev P, BatchDev bt, NbrDev nb, const double4 *rw4,
                                                         const int32_t *astruct, const void *bcoef_, void *vbuf_, int C,
                                                         int64_t n_items, unsigned long long *counter,
                                                         const void *tab_global) {
   constexpr int NG = nharm(LMAX - 1), NB = grad_block(LMAX);  // harmonics of the gradients, coefficients per slot
   extern __shared__ __align__(16) double lds_dyn[];
+  __shared__ int lds_k[STEP_K ? kMaxElements : 1];
   const int S = P.S, E = P.E;
   const double *__restrict__ tabg = (const double *)tab_global;
   double *tabl = lds_dyn;
@@ -426,10 +427,12 @@ __global__ __launch_bounds__(256, 2) void k_bwd_pairs64(PlanDev P, BatchDev bt, 
   const int tab_n = LDS ? S * E * BLKL : 0;
   if (LDS)
     for (int idx = threadIdx.x; idx < S * E * BLK; idx += blockDim.x) tabl[(idx / BLK) * BLKL + idx % BLK] = tabg[idx];
+  if (STEP_K)
+    for (int e = threadIdx.x; e < E; e += blockDim.x) lds_k[e] = P.kcount[e];
   __syncthreads();
   const int lane = lane_id();
   double *vbuf = (double *)vbuf_;
-  const int mask = P.order_mask, dens = P.dens_slot, kmx = P.kmax;
+  const int mask = P.order_mask, dens = P.dens_slot;
   double *bcoef = tabl + tab_n + (size_t)(threadIdx.x / kWave) * S * NB;
   for (;;) {
     const int64_t item = next_item(counter);
@@ -476,6 +479,7 @@ __global__ __launch_bounds__(256, 2) void k_bwd_pairs64(PlanDev P, BatchDev bt, 
       const double dz = (rjz - riz) + shz;
       const double q = (dx * dx + dy * dy) + dz * dz;
       const int e = shift_species(w);
+      const int K = STEP_K ? step_primitives(P.kmax, lds_k, e, act) : P.kmax;
       double Y[NG > 0 ? NG : 1];
       if constexpr (NG > 0)
         for_harmonics<LMAX - 1, false>(dx, dy, dz, [&](auto mc, double y) { Y[decltype(mc)::value] = y; });
@@ -490,7 +494,7 @@ __global__ __launch_bounds__(256, 2) void k_bwd_pairs64(PlanDev P, BatchDev bt, 
         auto primitives = [&](auto &&f) {
 #pragma unroll
           for (int kk = 0; kk < KB; ++kk) {
-            if (kk < kmx) {
+            if (kk < K) {
               const double *o = row + kk * kCoefStride;
               bool use = true;
               if constexpr (SCREEN) {  // per-primitive screening: the primitive's own radius
@@ -724,27 +728,30 @@ __global__ __launch_bounds__(256) void k_cell_reduce(BatchDev bt, const int64_t 
 using PairsFn = void (*)(PlanDev, BatchDev, NbrDev, const double4 *, const int32_t *, const void *, void *, int,
                          int64_t, unsigned long long *, const void *);
 // SCREEN: per-primitive screening (its own instantiation keeps the branch
-// out of the loop of plans without it)
-template <int L, int KB, bool F64, bool LDS, bool SCREEN> PairsFn pair_kernel() {
-  if constexpr (F64) return k_bwd_pairs64<L, KB, LDS, SCREEN>;
-  else return k_bwd_pairs<L, KB, LDS, SCREEN>;
+// out of the loop of plans without it); uneven: the elements' primitive counts
+// differ (FP64: a step's loops end with its own largest count)
+template <int L, int KB, bool F64, bool LDS, bool SCREEN> PairsFn pair_kernel(bool uneven) {
+  if constexpr (!F64) return k_bwd_pairs<L, KB, LDS, SCREEN>;
+  else if constexpr (!LDS || SCREEN) return k_bwd_pairs64<L, KB, LDS, SCREEN, true>;
+  else return uneven ? k_bwd_pairs64<L, KB, LDS, SCREEN, true> : k_bwd_pairs64<L, KB, LDS, SCREEN, false>;
 }
-template <int L, bool F64, bool LDS, bool SCREEN> PairsFn pick_kb(int kb) {
-  if (kb <= 4) return pair_kernel<L, 4, F64, LDS, SCREEN>();
-  if (kb <= 8) return pair_kernel<L, 8, F64, LDS, SCREEN>();
-  return pair_kernel<L, 16, F64, LDS, SCREEN>();
+template <int L, bool F64, bool LDS, bool SCREEN> PairsFn pick_kb(int kb, bool uneven) {
+  if (kb <= 4) return pair_kernel<L, 4, F64, LDS, SCREEN>(uneven);
+  if (kb <= 8) return pair_kernel<L, 8, F64, LDS, SCREEN>(uneven);
+  return pair_kernel<L, 16, F64, LDS, SCREEN>(uneven);
 }
-template <bool F64, bool LDS, bool SCREEN> PairsFn pick_l(int lmax, int kb) {
-  switch (lmax) {
-    case 0: return pick_kb<0, F64, LDS, SCREEN>(kb);
-    case 1: return pick_kb<1, F64, LDS, SCREEN>(kb);
-    case 2: return pick_kb<2, F64, LDS, SCREEN>(kb);
-    case 3: return pick_kb<3, F64, LDS, SCREEN>(kb);
-    default: return pick_kb<4, F64, LDS, SCREEN>(kb);
+template <bool F64, bool LDS, bool SCREEN> PairsFn pick_l(const PlanDev &P) {
+  const bool uneven = P.kmin < P.kmax;
+  switch (P.lmax) {
+    case 0: return pick_kb<0, F64, LDS, SCREEN>(P.kb, uneven);
+    case 1: return pick_kb<1, F64, LDS, SCREEN>(P.kb, uneven);
+    case 2: return pick_kb<2, F64, LDS, SCREEN>(P.kb, uneven);
+    case 3: return pick_kb<3, F64, LDS, SCREEN>(P.kb, uneven);
+    default: return pick_kb<4, F64, LDS, SCREEN>(P.kb, uneven);
   }
 }
-template <bool F64, bool LDS> PairsFn pick_pairs(int lmax, int kb, bool screen) {
-  return screen ? pick_l<F64, LDS, true>(lmax, kb) : pick_l<F64, LDS, false>(lmax, kb);
+template <bool F64, bool LDS> PairsFn pick_pairs(const PlanDev &P) {
+  return P.screen ? pick_l<F64, LDS, true>(P) : pick_l<F64, LDS, false>(P);
 }
 
 }  // namespace
@@ -805,11 +812,8 @@ void launch_backward(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, co
   const size_t tsm = (use_lds ? tab_bytes + (size_t)p->dev.S * p->dev.E * 16 : 0) +  // table with its gaps
                      4 * (size_t)p->dev.S * (f64 ? grad_block(p->dev.lmax) * 8 : coef_block(p->dev.lmax) * 4);
   const void *tab = f64 ? (const void *)p->dev.coef64 : (const void *)p->dev.coef32;
-  const bool scr = p->dev.screen != 0;
-  PairsFn fn = f64 ? (use_lds ? pick_pairs<true, true>(p->dev.lmax, p->dev.kb, scr)
-                              : pick_pairs<true, false>(p->dev.lmax, p->dev.kb, scr))
-                   : (use_lds ? pick_pairs<false, true>(p->dev.lmax, p->dev.kb, scr)
-                              : pick_pairs<false, false>(p->dev.lmax, p->dev.kb, scr));
+  PairsFn fn = f64 ? (use_lds ? pick_pairs<true, true>(p->dev) : pick_pairs<true, false>(p->dev))
+                   : (use_lds ? pick_pairs<false, true>(p->dev) : pick_pairs<false, false>(p->dev));
   int64_t pb = persistent_blocks((const void *)fn, tsm, p->tuning.blocks_per_cu);
   if (pb > (n_items + 3) / 4) pb = (n_items + 3) / 4;
   if (pb < 1) pb = 1;

@@ -467,7 +467,11 @@ gmp_status gmp_plan_create(const gmp_probe_desc *d, gmp_precision precision, gmp
   const size_t hbase = T.size();
   T.insert(T.end(), H.begin(), H.end());
   std::vector<int> kc(p->E);
-  for (int e = 0; e < p->E; ++e) kc[e] = d->prim_offsets[e + 1] - d->prim_offsets[e];
+  P.kmin = kmax;
+  for (int e = 0; e < p->E; ++e) {
+    kc[e] = d->prim_offsets[e + 1] - d->prim_offsets[e];
+    if (kc[e] < P.kmin) P.kmin = kc[e];
+  }
   // tabulated radial factors: per (slot, element) and interval [r_k, r_k+1]
   // of r = sqrt(q), the cubic Hermite interpolant of every c_l from its values
   // and r-derivatives at both ends, as coefficients of t = (r - r_k) / h

@@ -140,7 +140,7 @@ struct StructInfo {
 // order -1 when requested (dens_slot = -1 otherwise).  The density slot's
 // coefficient rows hold -beta (scaled), A_0 = B, A_1..A_4 = 0, -beta.
 struct PlanDev {
-  int S, E, n_orders, lmax, order_mask, kmax, kb, nf, ncomp_total;  // kb: primitive stride of the tables (4/8/16)
+  int S, E, n_orders, lmax, order_mask, kmin, kmax, kb, nf, ncomp_total;  // kb: primitive stride of the tables (4/8/16)
   int sub;                           // ranges of atom index per (shell, species) bucket in the neighbour build
   int n_sig, dens_slot, dens_order;  // sigmas, density slot, index of order -1 in orders (-1: none)
   int screen;                        // per-primitive screening (radius^2 in column 7 of the tables, FP32 value)
@@ -318,6 +318,17 @@ __device__ inline void for_harmonics(T x, T y, T z, F &&f) {
       }
     }
   }
+}
+
+// Largest primitive count (of at most kmax) among the elements e of the
+// wavefront's active lanes, one test per count above it.  The lists put the pairs
+// of one element beside each other, so that a step mostly meets one or two counts.
+// In FP64, elements of 1, 1, 2 and 16 primitives, 1500 atoms: overlap 0.33 -> 0.21,
+// adjoint 0.46 -> 0.30 ms.
+__device__ inline int step_primitives(int kmax, const int *counts, int e, bool active) {
+  const int own = active ? counts[e] : 0;
+  while (kmax > 0 && __ballot(own >= kmax) == 0) --kmax;
+  return kmax;
 }
 
 // Structure of index g (atom or reference point).

@@ -268,8 +268,7 @@ __device__ inline void radial_sums(const float *const (&row)[NU], float q, int k
   }
 }
 template <int LMAX, int KB, int NU>
-__device__ inline void radial_sums(const double *const (&row)[NU], double q, int kmax,
-                                   double (&cl)[NU][LMAX + 1]) {
+__device__ inline void radial_sums(const double *const (&row)[NU], double q, int kmax, double (&cl)[NU][LMAX + 1]) {
   for (int k = 0; k < kmax; ++k) {
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
@@ -303,7 +302,7 @@ __device__ inline void radial_sums(const double *const (&row)[NU], double q, int
 // is copied into LDS once per workgroup when it fits, with a 16-byte gap
 // after every (slot, element) block: lanes of different species read their
 // rows from different banks.
-template <int LMAX, int KB, int MODE, bool LDS, bool SCREEN, bool OCC, bool TAB = false>
+template <int LMAX, int KB, int MODE, bool LDS, bool SCREEN, bool OCC, bool TAB = false, bool STEP_K = false>
 __global__ __launch_bounds__(256, pass_slots(MODE, LMAX) == 1 ? 3 : 2) void k_overlap(PlanDev P, BatchDev bt, NbrDev nb, const double4 *rw4,
                                                     const int32_t *astruct, double *partial,
                                                     const int64_t *chunk_off, int kc, int ng,
@@ -320,6 +319,9 @@ __global__ __launch_bounds__(256, pass_slots(MODE, LMAX) == 1 ? 3 : 2) void k_ov
     const int n = S * E * BLK;
     for (int idx = threadIdx.x; idx < n; idx += blockDim.x) tabl[(idx / BLK) * BLKL + idx % BLK] = tabg[idx];
   }
+  __shared__ int lds_k[STEP_K ? kMaxElements : 1];
+  if (STEP_K)
+    for (int e = threadIdx.x; e < E; e += blockDim.x) lds_k[e] = P.kcount[e];
   __syncthreads();
 
   const int lane = lane_id();
@@ -428,6 +430,7 @@ __global__ __launch_bounds__(256, pass_slots(MODE, LMAX) == 1 ? 3 : 2) void k_ov
         // radial factors of the pass's slots; zero past a slot's own prefix
         TR cl[NS][LMAX + 1];
         const int tl = ta * NS;
+        const int K = STEP_K ? step_primitives(P.kmax, lds_k, e, p < pass_end(ta)) : P.kmax;
         if (NS > 1 && !SCREEN && !TAB && tl + NS <= S && pa < slot_end(tl)) {  // every slot takes pairs of this step
           const TR *row[NS];
 #pragma unroll
@@ -436,7 +439,7 @@ __global__ __launch_bounds__(256, pass_slots(MODE, LMAX) == 1 ? 3 : 2) void k_ov
 #pragma unroll
             for (int l = 0; l <= LMAX; ++l) cl[u][l] = (TR)0;
           }
-          radial_sums<LMAX, KB, NS>(row, qv, P.kmax, cl);
+          radial_sums<LMAX, KB, NS>(row, qv, K, cl);
           // nothing from the lanes past a slot's prefix: a step in which any
           // prefix of the pass ends is one in which the shortest does
           if (slot_end(tl) - pa < kWave) {
@@ -463,7 +466,7 @@ __global__ __launch_bounds__(256, pass_slots(MODE, LMAX) == 1 ? 3 : 2) void k_ov
                 // the primitive's own radius; skipped by the wavefront when no lane needs it
 #pragma unroll
                 for (int k = 0; k < KB; ++k) {
-                  if (k < P.kmax) {
+                  if (k < K) {
                     const TR *o = row[0] + k * kCoefStride;
                     const bool use = (float)q <= (float)o[7];
                     if (__ballot(use) == 0) continue;
@@ -476,7 +479,7 @@ __global__ __launch_bounds__(256, pass_slots(MODE, LMAX) == 1 ? 3 : 2) void k_ov
                 TR c1[1][LMAX + 1];
 #pragma unroll
                 for (int l = 0; l <= LMAX; ++l) c1[0][l] = (TR)0;
-                radial_sums<LMAX, KB, 1>(row, qv, P.kmax, c1);
+                radial_sums<LMAX, KB, 1>(row, qv, K, c1);
 #pragma unroll
                 for (int l = 0; l <= LMAX; ++l) cl[u][l] = c1[0][l];
               }
@@ -652,26 +655,35 @@ using OverlapFn = void (*)(PlanDev, BatchDev, NbrDev, const double4 *, const int
 
 // SCREEN: per-primitive screening; OCC: the neighbours' occupancies scale the
 // terms (without occupancies they are 1, so the variants that are not on the
-// common path always multiply)
-template <int L, int MODE, bool LDS, bool SCREEN, bool OCC> OverlapFn pick_k(int kb) {
-  if (kb <= 4) return k_overlap<L, 4, MODE, LDS, SCREEN, OCC>;
-  if (kb <= 8) return k_overlap<L, 8, MODE, LDS, SCREEN, OCC>;
-  return k_overlap<L, 16, MODE, LDS, SCREEN, OCC>;
+// common path always multiply); STEP_K: a step's primitive loops end with the
+// largest count among its own elements, where an exponential is dear (FP64) or a
+// row is tested before it is used (SCREEN).  With one count for all elements the
+// plan's is as good, and the test alone costs (l <= 2, FP64, 1500 atoms: 0.14 ->
+// 0.16 ms).
+template <int L, int MODE, bool LDS, bool SCREEN, bool OCC, bool STEP_K> OverlapFn pick_k(int kb) {
+  if (kb <= 4) return k_overlap<L, 4, MODE, LDS, SCREEN, OCC, false, STEP_K>;
+  if (kb <= 8) return k_overlap<L, 8, MODE, LDS, SCREEN, OCC, false, STEP_K>;
+  return k_overlap<L, 16, MODE, LDS, SCREEN, OCC, false, STEP_K>;
 }
-template <int MODE, bool LDS, bool SCREEN, bool OCC> OverlapFn pick_l(int lmax, int kb) {
+template <int MODE, bool LDS, bool SCREEN, bool OCC, bool STEP_K> OverlapFn pick_l(int lmax, int kb) {
   switch (lmax) {
-    case 0: return pick_k<0, MODE, LDS, SCREEN, OCC>(kb);
-    case 1: return pick_k<1, MODE, LDS, SCREEN, OCC>(kb);
-    case 2: return pick_k<2, MODE, LDS, SCREEN, OCC>(kb);
-    case 3: return pick_k<3, MODE, LDS, SCREEN, OCC>(kb);
-    default: return pick_k<4, MODE, LDS, SCREEN, OCC>(kb);
+    case 0: return pick_k<0, MODE, LDS, SCREEN, OCC, STEP_K>(kb);
+    case 1: return pick_k<1, MODE, LDS, SCREEN, OCC, STEP_K>(kb);
+    case 2: return pick_k<2, MODE, LDS, SCREEN, OCC, STEP_K>(kb);
+    case 3: return pick_k<3, MODE, LDS, SCREEN, OCC, STEP_K>(kb);
+    default: return pick_k<4, MODE, LDS, SCREEN, OCC, STEP_K>(kb);
   }
 }
-template <int MODE> OverlapFn pick_overlap(int lmax, int kb, bool lds, bool screen, bool occ) {
-  if (screen) return lds ? pick_l<MODE, true, true, true>(lmax, kb) : pick_l<MODE, false, true, true>(lmax, kb);
-  if (!lds) return pick_l<MODE, false, false, true>(lmax, kb);
-  if constexpr (MODE == ACC_TERMS) return pick_l<MODE, true, false, true>(lmax, kb);
-  else return occ ? pick_l<MODE, true, false, true>(lmax, kb) : pick_l<MODE, true, false, false>(lmax, kb);
+template <int MODE> OverlapFn pick_overlap(const PlanDev &P, bool lds, bool occ) {
+  const int lmax = P.lmax, kb = P.kb;
+  constexpr bool F64 = MODE == ACC_F64;
+  if (P.screen)
+    return lds ? pick_l<MODE, true, true, true, true>(lmax, kb) : pick_l<MODE, false, true, true, true>(lmax, kb);
+  if (!lds) return pick_l<MODE, false, false, true, F64>(lmax, kb);
+  if constexpr (F64)
+    if (P.kmin < P.kmax) return pick_l<MODE, true, false, true, true>(lmax, kb);
+  if constexpr (MODE == ACC_TERMS) return pick_l<MODE, true, false, true, false>(lmax, kb);
+  else return occ ? pick_l<MODE, true, false, true, false>(lmax, kb) : pick_l<MODE, true, false, false, false>(lmax, kb);
 }
 
 // tabulated radial factors (FP32 modes): no coefficient table, no primitive loop
@@ -802,12 +814,11 @@ void launch_overlap(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, dou
   const bool use_lds = tab_bytes <= 48 * 1024 && !tabulated;
   const size_t smem = use_lds ? tab_bytes + (size_t)p->dev.S * p->dev.E * 16 : 0;  // with its gaps
   const void *tab = f64 ? (const void *)p->dev.coef64 : (const void *)p->dev.coef32;
-  const bool screen = p->dev.screen != 0, occ = bt.occ != nullptr;
-  const int kb = p->dev.kb;
-  OverlapFn fn = tabulated ? (mode == ACC_TERMS ? pick_tab<ACC_TERMS>(lmax) : pick_tab<ACC_WIDE>(lmax))
-                 : f64     ? pick_overlap<ACC_F64>(lmax, kb, use_lds, screen, occ)
-                 : mode == ACC_TERMS ? pick_overlap<ACC_TERMS>(lmax, kb, use_lds, screen, occ)
-                                     : pick_overlap<ACC_WIDE>(lmax, kb, use_lds, screen, occ);
+  const bool occ = bt.occ != nullptr;
+  OverlapFn fn = tabulated           ? (mode == ACC_TERMS ? pick_tab<ACC_TERMS>(lmax) : pick_tab<ACC_WIDE>(lmax))
+                 : f64               ? pick_overlap<ACC_F64>(p->dev, use_lds, occ)
+                 : mode == ACC_TERMS ? pick_overlap<ACC_TERMS>(p->dev, use_lds, occ)
+                                     : pick_overlap<ACC_WIDE>(p->dev, use_lds, occ);
   int64_t blocks = persistent_blocks((const void *)fn, smem, p->tuning.blocks_per_cu);
   // no more wavefronts than items: with some idle, those with an item would sit unevenly on the SIMDs
   const int64_t whole = kc > 0 ? pairs_bound / kc : 0;

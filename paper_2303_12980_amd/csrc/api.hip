@@ -347,10 +347,13 @@ gmp_status gmp_plan_create(const gmp_probe_desc *d, gmp_precision precision, gmp
   P.n_orders = p->n_orders;
   P.order_mask = mask;
   P.kmax = kmax;
-  // The neighbour build orders a bucket's keys by counting, within ranges of
-  // atom indices of a few dozen keys; 256 to 512 counters a centre (l <= 4
-  // plans of 4096 to 60,000 atoms: 166 keys in the buckets of the first shell).
-  P.sub = P.S * P.E <= 48 ? 8 : (P.S * P.E <= 96 ? 4 : (P.S * P.E <= 192 ? 2 : 1));
+  // The neighbour build orders a bucket's keys by counting, within ranges of atom
+  // indices of a few dozen keys: the most ranges of a bucket that a build takes,
+  // 32 to 1 (with more than one at most 384 counters a centre, else S x E of
+  // them, up to 1024).  At most 8 before: 1200 atoms, 8 buckets, fill 0.050 ->
+  // 0.044, reverse 0.049 -> 0.042 ms; 3000 atoms, 24 buckets, 0.074 -> 0.070 ms.
+  P.sub = 1;
+  while (P.sub < 32 && 2 * P.sub * P.S * P.E <= 384) P.sub *= 2;
   const int kb = kmax <= 4 ? 4 : (kmax <= 8 ? 8 : 16);
   P.kb = kb;
   P.lmax = 0;
@@ -725,7 +728,7 @@ static int64_t lds_per_block() {
 // to the long-list kernel, which sorts with the most LDS a workgroup may hold
 // (its static LDS, candidate staging and bucket counters, takes up to
 // kFillStaticLds bytes).
-constexpr int64_t kFillStaticLds = 12 * 1024;  // (and the counters per range of atom indices, up to 2.7 KB)
+constexpr int64_t kFillStaticLds = 12 * 1024;  // (and the counters per range of atom indices, up to 3 KB)
 constexpr int64_t kShortSortMax = 8192;
 int long_keys_for(const gmp_plan *p) {
   const int nbk = p->dev.E * p->dev.S;

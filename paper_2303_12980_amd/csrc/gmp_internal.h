@@ -141,7 +141,7 @@ struct StructInfo {
 // coefficient rows hold -beta (scaled), A_0 = B, A_1..A_4 = 0, -beta.
 struct PlanDev {
   int S, E, n_orders, lmax, order_mask, kmin, kmax, kb, nf, ncomp_total;  // kb: primitive stride of the tables (4/8/16)
-  int sub;                           // ranges of atom index per (shell, species) bucket in the neighbour build
+  int sub;                           // ranges of atom index per (shell, species) bucket: of a plan the most, of a build its own
   int n_sig, dens_slot, dens_order;  // sigmas, density slot, index of order -1 in orders (-1: none)
   int screen;                        // per-primitive screening (radius^2 in column 7 of the tables, FP32 value)
   int tab_n;                         // tabulated radial factors: intervals per (slot, element) (0: exact)

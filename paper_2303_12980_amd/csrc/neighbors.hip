@@ -966,12 +966,31 @@ __global__ __launch_bounds__(256) void k_reverse(PlanDev P, BatchDev bt, NbrDev 
 }  // namespace
 
 // ------------------------------------------------------------------ host launchers
+// The plan with the number of index ranges per bucket of one build: a power of
+// two, as many as the plan allows (384 counters a centre), but no more than a
+// structure has atoms and no more counters than an average list has room for
+// entries, past which they cost the count and the fill more than the shorter
+// ranges save.  With up to 8 ranges whatever the batch: 4096 molecules of 9-29
+// atoms, lists 0.600 ms, now 0.557; 2048 cells of 1-4 atoms 1.17, now 1.12; with
+// few buckets, 20,000 atoms in spatial order (whose neighbours share one to three
+// ranges of 8), 4 slots x 2 species, count + fill + reverse 2.06, now 1.70.
+// Depends on the batch's sizes and the capacity alone, which gmp_build_lists and
+// gmp_build_reverse have in common.
+static PlanDev plan_of_build(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb) {
+  PlanDev P = p->dev;
+  const int64_t nc = n_centres(bt), entries = nc > 0 ? nb.capacity / nc : 0;
+  const int64_t atoms = bt.n_structs > 0 ? (bt.n_atoms + bt.n_structs - 1) / bt.n_structs : 0;
+  while (P.sub > 1 && (P.sub > atoms || (int64_t)P.S * P.E * P.sub > entries)) P.sub /= 2;
+  return P;
+}
+
 // Cell list: wrap, bins, bin-sorted atoms.  Small batches in one workgroup.
 void launch_cells(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, const WsLayout &L, hipStream_t s) {
   const int64_t n = n_total(bt), n_bins = bt.n_atoms + bt.n_structs;
   const double rcmax = sqrt(p->dev.rcmax2);
+  const PlanDev P = plan_of_build(p, bt, nb);
   if (n <= kSmallAtoms && bt.n_structs <= kSmallAtoms) {
-    GMP_LAUNCH("nbr_small_cells", k_small_cells, dim3(1), dim3(kScanThreads), 0, s, p->dev, bt, nb, L.sinfo, rcmax,
+    GMP_LAUNCH("nbr_small_cells", k_small_cells, dim3(1), dim3(kScanThreads), 0, s, P, bt, nb, L.sinfo, rcmax,
                p->tuning.bin_divisor, L.status, L.bin_count, L.bin_start, L.bin_fill, L.fw, L.bin_of, L.astruct,
                L.range_col, L.sid_tmp, L.sx, L.sy, L.sz, L.sid, L.ssp);
     return;
@@ -981,7 +1000,7 @@ void launch_cells(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, const
   GMP_LAUNCH("nbr_setup", k_setup, blocks_of(n_bins > 64 ? n_bins : 64), dim3(256), 0, s, bt, L.sinfo, rcmax,
              p->tuning.bin_divisor, L.status, L.bin_count, L.bin_fill, n_bins);
   GMP_LAUNCH("nbr_wrap", k_wrap, blocks_of(wraps), dim3(256), 0, s, bt, L.sinfo, nb, L.fw, L.bin_of, L.bin_count,
-             L.astruct, L.range_col, p->dev, L.status);
+             L.astruct, L.range_col, P, L.status);
   scan_i32_to_i64(L.bin_count, L.bin_start, n_bins, L.scan_aux, s);
   if (bt.n_atoms == 0) return;
   GMP_LAUNCH("nbr_scatter", k_scatter, blocks_of(bt.n_atoms), dim3(256), 0, s, bt, L.bin_of, L.bin_start, L.bin_fill,
@@ -993,9 +1012,10 @@ void launch_cells(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, const
 void launch_count(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, const WsLayout &L, hipStream_t s) {
   int64_t blocks = n_centres(bt);
   if (blocks == 0) return;
-  size_t smem = sizeof(int32_t) * p->dev.E * p->dev.S * p->dev.sub;
+  const PlanDev P = plan_of_build(p, bt, nb);
+  size_t smem = sizeof(int32_t) * P.E * P.S * P.sub;
   auto kern = p->dev.S <= 8 ? k_count<8> : (p->dev.S <= 12 ? k_count<12> : k_count<kMaxSigmas>);
-  GMP_LAUNCH("nbr_count", kern, dim3((unsigned)blocks), dim3(256), smem, s, p->dev, bt, nb, L.sinfo, L.fw,
+  GMP_LAUNCH("nbr_count", kern, dim3((unsigned)blocks), dim3(256), smem, s, P, bt, nb, L.sinfo, L.fw,
              L.bin_start, L.sx, L.sy, L.sz, L.sid, L.ssp, L.astruct, L.cnt, L.ptotal, L.bucket_max, L.status);
 }
 
@@ -1014,19 +1034,20 @@ void launch_offsets(const BatchDev &bt, const WsLayout &L, int64_t *offsets, boo
 
 void launch_fill(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, const WsLayout &L, int lds_keys,
                  int long_keys, hipStream_t s) {
-  int nbk = p->dev.E * p->dev.S;
+  const PlanDev P = plan_of_build(p, bt, nb);
+  const int nbk = P.E * P.S;
   if (n_centres(bt) == 0) return;
   uint64_t *pk = (nb.reverse && !point_mode(bt)) ? L.pair_key : (uint64_t *)nullptr;
-  size_t smem = sizeof(uint64_t) * (lds_keys + kKeyPad) + sizeof(int32_t) * (2 * nbk * p->dev.sub + 2);
+  size_t smem = sizeof(uint64_t) * (lds_keys + kKeyPad) + sizeof(int32_t) * (2 * nbk * P.sub + 2);
   auto kern = p->dev.S <= 8 ? k_fill<8> : (p->dev.S <= 12 ? k_fill<12> : k_fill<kMaxSigmas>);
-  GMP_LAUNCH("nbr_fill_sort", kern, dim3((unsigned)n_centres(bt)), dim3(256), smem, s, p->dev, bt, nb, L.sinfo,
+  GMP_LAUNCH("nbr_fill_sort", kern, dim3((unsigned)n_centres(bt)), dim3(256), smem, s, P, bt, nb, L.sinfo,
              L.fw, L.bin_start, L.sx, L.sy, L.sz, L.sid, L.ssp, L.astruct, L.cnt, lds_keys, pk, L.pair_centre,
              L.range_start, L.status, L.long_q);
   if (long_keys > 0) {  // one workgroup per CU (its LDS takes most of the CU's), capped by the centre count
-    smem = sizeof(uint64_t) * (long_keys + kKeyPad) + sizeof(int32_t) * (2 * nbk * p->dev.sub + 2);
+    smem = sizeof(uint64_t) * (long_keys + kKeyPad) + sizeof(int32_t) * (2 * nbk * P.sub + 2);
     const int64_t blocks = n_centres(bt) < 256 ? n_centres(bt) : 256;
     auto kern_long = p->dev.S <= 8 ? k_fill_long<8> : (p->dev.S <= 12 ? k_fill_long<12> : k_fill_long<kMaxSigmas>);
-    GMP_LAUNCH("nbr_fill_long", kern_long, dim3((unsigned)blocks), dim3(256), smem, s, p->dev, bt, nb, L.sinfo,
+    GMP_LAUNCH("nbr_fill_long", kern_long, dim3((unsigned)blocks), dim3(256), smem, s, P, bt, nb, L.sinfo,
                L.fw, L.bin_start, L.sx, L.sy, L.sz, L.sid, L.ssp, L.astruct, L.cnt, long_keys, pk, L.pair_centre,
                L.range_start, L.status, L.long_q);
   }
@@ -1037,7 +1058,7 @@ void launch_reverse(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, con
   // every entry of every written list was set to -1 (unresolved) by the fill
   const int64_t blocks = (n_pairs + 255) / 256;
   if (blocks > 0)
-    GMP_LAUNCH("nbr_reverse", k_reverse, dim3((unsigned)blocks), dim3(256), 0, s, p->dev, bt, nb, L.pair_key,
+    GMP_LAUNCH("nbr_reverse", k_reverse, dim3((unsigned)blocks), dim3(256), 0, s, plan_of_build(p, bt, nb), bt, nb, L.pair_key,
                L.pair_centre, L.range_start, L.range_col, n_pairs, L.status);
 }
 

@@ -220,10 +220,11 @@ gmp_status gmp_plan_info(const gmp_plan *plan, int32_t *n_features, int32_t *n_c
  *                 kernels (equal pieces of the list; 0 = automatic: about
  *                 8,192 items over the batch, none shorter than chunk_pairs).
  *  sigma_groups:  each forward work item (a chunk of a list) is split into
- *                 this many work items, each taking one group of the cutoff
- *                 slots in cutoff order (1..16, capped at the slot count;
- *                 0 = 1); finer items for the persistent grid, the same
- *                 features bit for bit.
+ *                 at least this many work items, each taking one group of the
+ *                 passes over the cutoff slots (1..16, capped at the number of
+ *                 passes; 0 = 1; small batches take more by themselves); finer
+ *                 items for the persistent grid, the same features bit for
+ *                 bit and the same workspace.
  * The workspace size depends on the tuning.  Changing the tuning is not
  * thread-safe with concurrent calls on the plan. */
 typedef struct {

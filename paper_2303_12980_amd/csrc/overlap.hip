@@ -735,20 +735,17 @@ void *noalloc_scratch(size_t *bytes, hipError_t *err) {
 int chunk_size(const gmp_plan *p) { return p->tuning.chunk_pairs > 0 ? p->tuning.chunk_pairs : 0; }
 
 // groups of cutoff slots per chunk that the tuning asks for
-int slot_groups(const gmp_plan *p) {
+static int slot_groups(const gmp_plan *p) {
   const int g = p->tuning.sigma_groups > 0 ? p->tuning.sigma_groups : 1;
   return g < p->dev.S ? g : (p->dev.S > 0 ? p->dev.S : 1);
 }
 
-// upper bound on the number of chunks of a batch with at most `pairs` pairs
-static int64_t chunks_bound(const gmp_plan *p, int64_t n_atoms, int64_t pairs) {
+// Upper bound on the number of chunks of a batch with at most `pairs` pairs: the
+// rows of partial moments it is given room for (groups of passes share a row, each
+// writing its own slots).
+int64_t max_chunks(const gmp_plan *p, int64_t n_atoms, int64_t pairs) {
   const int kc = chunk_size(p);
   return n_atoms + (kc > 0 ? pairs / kc + 1 : 0);
-}
-
-// rows of partial moments a batch is given room for
-int64_t max_chunks(const gmp_plan *p, int64_t n_atoms, int64_t pairs) {
-  return chunks_bound(p, n_atoms, pairs) * slot_groups(p);
 }
 
 // Groups of passes per chunk (each a work item of its own): what the tuning

@@ -840,7 +840,9 @@ __device__ inline void fill_centre(const PlanDev &P, const BatchDev &bt, const N
           for (int m = b0; m < b1; ++m) r += keys[m] < key ? 1 : 0;
         }
       }
-      if (r >= n_keys) { atomicOr(status, ST_INTERNAL); return; }
+      // never for lists that were counted alike; were positions changed under the build, a key
+      // left over in LDS could name a range of another pass: nothing outside the list is written
+      if ((uint32_t)r >= (uint32_t)n_keys) { atomicOr(status, ST_INTERNAL); return; }
       const int64_t at = base + key0 + r;
       const uint32_t n1 = (uint32_t)key_shift(key, 0) & 0xffu;
       const uint32_t n2 = (uint32_t)key_shift(key, 1) & 0xffu;

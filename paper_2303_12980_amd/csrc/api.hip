@@ -26,7 +26,7 @@ void launch_overlap(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, dou
                     int32_t *astruct, int64_t pairs_bound, bool components, hipStream_t s);
 void launch_finish(const gmp_plan *p, int64_t N, const double *partial, const int64_t *chunk_off,
                    const int32_t *order, void *features,
-                   double *components, hipStream_t s);
+                   double *components, unsigned long long *counter, hipStream_t s);
 void *noalloc_scratch(size_t *bytes, hipError_t *err);
 size_t bwd_coef_elems(const gmp_plan *p, int64_t n_atoms);
 void launch_backward(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, const double *components,
@@ -866,7 +866,7 @@ gmp_status gmp_features(const gmp_plan *p, const gmp_batch *b, const gmp_neighbo
   const int64_t pairs = n->n_pairs > 0 && n->n_pairs <= n->capacity ? n->n_pairs : n->capacity;
   launch_overlap(p, bt, nb, L.partial, L.nch, L.chunk_off, L.scan_aux, L.counter, L.rw4, L.astruct, pairs,
                  components != nullptr, s);
-  launch_finish(p, N, L.partial, L.chunk_off, n->order, features, components, s);
+  launch_finish(p, N, L.partial, L.chunk_off, n->order, features, components, L.counter, s);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_error(e, "feature kernels");
   return GMP_OK;
@@ -904,7 +904,7 @@ gmp_status gmp_features_noalloc(const gmp_plan *p, const gmp_batch *b, const gmp
   hipStream_t s = (hipStream_t)stream;
   launch_overlap(p, to_dev(b), to_dev(n), partial, nch, chunk_off, scan_aux, counter, rw4, astruct, pairs,
                  components != nullptr, s);
-  launch_finish(p, N, partial, chunk_off, n->order, features, components, s);
+  launch_finish(p, N, partial, chunk_off, n->order, features, components, counter, s);
   e = hipGetLastError();
   if (e != hipSuccess) return hip_error(e, "feature kernels");
   return GMP_OK;

@@ -424,7 +424,7 @@ struct WsLayout {
   double *partial;        // overlap partial moments [chunk][slot][harmonic]
   int64_t *nch;           // [N] chunks per centre
   int64_t *chunk_off;     // [N+1] first chunk of each centre
-  unsigned long long *counter;  // work-item counter of the persistent kernels
+  unsigned long long *counter;  // work-item counter of the persistent kernels; [1]: a position has diverged (forward)
   double4 *rw4;           // [N] AoS copy of the wrapped positions
   uint64_t *pair_key;     // [capacity] packed (j, n) of every pair (reverse search)
   int32_t *pair_centre;   // [capacity] centre of every pair (reverse search)

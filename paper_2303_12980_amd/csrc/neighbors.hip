@@ -121,12 +121,14 @@ __device__ inline void struct_setup(const BatchDev &bt, StructInfo *info, int s,
   info[s] = I;
 }
 
-// Clears the status words and the bin counters, and sets up the structures.
+// Clears the status words, the forward's word for diverged positions and the bin
+// counters, and sets up the structures.
 __global__ __launch_bounds__(256) void k_setup(BatchDev bt, StructInfo *info, double rcmax, int bin_div,
-                                               uint32_t *status, int32_t *bin_count, int32_t *bin_fill,
+                                               uint32_t *status, unsigned long long *counter, int32_t *bin_count, int32_t *bin_fill,
                                                int64_t n_bins) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < 64) status[i] = 0u;
+  if (i == 0) counter[1] = 0ull;
   if (i < n_bins) { bin_count[i] = 0; bin_fill[i] = 0; }
   if (i < bt.n_structs) struct_setup(bt, info, (int)i, rcmax, bin_div);
 }
@@ -287,7 +289,7 @@ __global__ void k_bin_order(BatchDev bt, NbrDev nb, const int32_t *bin_of, const
 constexpr int kSmallAtoms = 1024;
 __global__ __launch_bounds__(kScanThreads) void k_small_cells(PlanDev P, BatchDev bt, NbrDev nb, StructInfo *info,
                                                               double rcmax, int bin_div, uint32_t *status,
-                                                              int32_t *bin_count, int64_t *bin_start,
+                                                              unsigned long long *counter, int32_t *bin_count, int64_t *bin_start,
                                                               int32_t *bin_fill, double *fw, int32_t *bin_of,
                                                               int32_t *astruct, int32_t *range_col, int32_t *sid_tmp,
                                                               double *sx, double *sy, double *sz, int32_t *sid,
@@ -296,6 +298,7 @@ __global__ __launch_bounds__(kScanThreads) void k_small_cells(PlanDev P, BatchDe
   const int t = threadIdx.x;  // at least as many threads as structures, atoms and points, and half the bins
   const int64_t n_bins = bt.n_atoms + bt.n_structs;
   if (t < 64) status[t] = 0u;
+  if (t == 0) counter[1] = 0ull;
   for (int64_t i = t; i < n_bins; i += kScanThreads) { bin_count[i] = 0; bin_fill[i] = 0; }
   if (t < bt.n_structs) struct_setup(bt, info, t, rcmax, bin_div);
   __syncthreads();
@@ -993,14 +996,14 @@ void launch_cells(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, const
   const PlanDev P = plan_of_build(p, bt, nb);
   if (n <= kSmallAtoms && bt.n_structs <= kSmallAtoms) {
     GMP_LAUNCH("nbr_small_cells", k_small_cells, dim3(1), dim3(kScanThreads), 0, s, P, bt, nb, L.sinfo, rcmax,
-               p->tuning.bin_divisor, L.status, L.bin_count, L.bin_start, L.bin_fill, L.fw, L.bin_of, L.astruct,
+               p->tuning.bin_divisor, L.status, L.counter, L.bin_count, L.bin_start, L.bin_fill, L.fw, L.bin_of, L.astruct,
                L.range_col, L.sid_tmp, L.sx, L.sy, L.sz, L.sid, L.ssp);
     return;
   }
   auto blocks_of = [](int64_t items) { return dim3((unsigned)((items + 255) / 256)); };
   const int64_t wraps = n > bt.n_structs ? n : bt.n_structs;  // a thread per structure reports its faults
   GMP_LAUNCH("nbr_setup", k_setup, blocks_of(n_bins > 64 ? n_bins : 64), dim3(256), 0, s, bt, L.sinfo, rcmax,
-             p->tuning.bin_divisor, L.status, L.bin_count, L.bin_fill, n_bins);
+             p->tuning.bin_divisor, L.status, L.counter, L.bin_count, L.bin_fill, n_bins);
   GMP_LAUNCH("nbr_wrap", k_wrap, blocks_of(wraps), dim3(256), 0, s, bt, L.sinfo, nb, L.fw, L.bin_of, L.bin_count,
              L.astruct, L.range_col, P, L.status);
   scan_i32_to_i64(L.bin_count, L.bin_start, n_bins, L.scan_aux, s);

@@ -56,7 +56,10 @@ __device__ inline double exp_scaled(double a, double q) { return exp(a * q); }
 // own list only and a batched launch sums in the same order as a launch over
 // one structure), its structure, and its wrapped position as an AoS double4
 // (one 32-byte gather per neighbour).  The first thread also clears the
-// work-item counter.
+// work-item counter.  The word after the counter tells the overlap kernel of a
+// position that has diverged since the lists were built (kFar).  The neighbour
+// build clears it, and the norm kernel behind the overlap; a stale one costs time
+// only.
 // Indices g < n_total get their structure and packed position; centres
 // c < n_centres their chunk count.
 __device__ inline int64_t list_chunks(const NbrDev &nb, int kc, int64_t k) {
@@ -65,18 +68,25 @@ __device__ inline int64_t list_chunks(const NbrDev &nb, int kc, int64_t k) {
   // build, reported in the status word): no work items, zero moments
   return end > nb.capacity ? 0 : (kc > 0 && cnt > kc ? (cnt + kc - 1) / kc : 1);
 }
-__device__ inline void prep_index(const BatchDev &bt, const NbrDev &nb, double4 *rw4, int32_t *astruct, int64_t i) {
+constexpr double kFar = 1e12;  // monomials of degree 3 do not overflow in FP32 below twice that
+__device__ inline bool far(const double4 &r) {
+  return !(__builtin_fabs(r.x) < kFar && __builtin_fabs(r.y) < kFar && __builtin_fabs(r.z) < kFar);
+}
+__device__ inline void prep_index(const BatchDev &bt, const NbrDev &nb, double4 *rw4, int32_t *astruct,
+                                  unsigned long long *counter, int64_t i) {
   if (i >= n_total(bt)) return;
   const int st = struct_of_index(bt, i);
   astruct[i] = st;
-  rw4[i] = wrapped_position(bt, nb, i, st);
+  const double4 r = wrapped_position(bt, nb, i, st);
+  rw4[i] = r;
+  if (far(r)) atomicOr(counter + 1, 1ull);
 }
 __global__ void k_overlap_prep(BatchDev bt, NbrDev nb, int kc, int64_t *nch, double4 *rw4, int32_t *astruct,
                                unsigned long long *counter) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i == 0) *counter = 0ull;
   if (i < n_centres(bt)) nch[i] = list_chunks(nb, kc, i);
-  prep_index(bt, nb, rw4, astruct, i);
+  prep_index(bt, nb, rw4, astruct, counter, i);
 }
 // The same with the scan of the chunk counts, which needs nothing of the rest,
 // in the first workgroup: one launch where one workgroup can scan them.
@@ -88,7 +98,7 @@ __global__ __launch_bounds__(kScanThreads) void k_overlap_prep_scan(BatchDev bt,
     if (threadIdx.x == 0) *counter = 0ull;
     block_scan([&](int64_t k) { return list_chunks(nb, kc, k); }, chunk_off, n_centres(bt), words);
   } else {
-    prep_index(bt, nb, rw4, astruct, (int64_t)(blockIdx.x - 1) * kScanThreads + threadIdx.x);
+    prep_index(bt, nb, rw4, astruct, counter, (int64_t)(blockIdx.x - 1) * kScanThreads + threadIdx.x);
   }
 }
 
@@ -302,30 +312,16 @@ __device__ inline void radial_sums(const double *const (&row)[NU], double q, int
 // is copied into LDS once per workgroup when it fits, with a 16-byte gap
 // after every (slot, element) block: lanes of different species read their
 // rows from different banks.
-template <int LMAX, int KB, int MODE, bool LDS, bool SCREEN, bool OCC, bool TAB = false, bool STEP_K = false>
-__global__ __launch_bounds__(256, pass_slots(MODE, LMAX) == 1 ? 3 : 2) void k_overlap(PlanDev P, BatchDev bt, NbrDev nb, const double4 *rw4,
-                                                    const int32_t *astruct, double *partial,
-                                                    const int64_t *chunk_off, int kc, int ng,
-                                                    int nbatch, unsigned long long *counter, const void *tab_global) {
-  using TR = typename std::conditional<MODE == ACC_F64, double, float>::type;  // radial arithmetic
-  constexpr int NH = n_moments(MODE, LMAX), NS = pass_slots(MODE, LMAX);
+template <int LMAX, int KB, int MODE, bool LDS, bool SCREEN, bool OCC, bool TAB, bool STEP_K, int NS, typename TR>
+__device__ __forceinline__ void overlap_items(const PlanDev &P, const BatchDev &bt, const NbrDev &nb,
+                                              const double4 *rw4, const int32_t *astruct, double *partial,
+                                              const int64_t *chunk_off, int kc, int ng, int nbatch,
+                                              unsigned long long *counter, const TR *__restrict__ tabg,
+                                              const TR *tabl, const int *lds_k, double *red) {
+  constexpr int NH = n_moments(MODE, LMAX);
   constexpr int BLK = KB * kCoefStride, BLKL = BLK + 16 / (int)sizeof(TR);
-  extern __shared__ __align__(16) double lds_dyn[];
-  __shared__ __align__(16) double lds_red[4][red_doubles(NH)];
   const int S = P.S, E = P.E;
-  const TR *__restrict__ tabg = (const TR *)tab_global;
-  TR *tabl = (TR *)lds_dyn;
-  if (LDS) {
-    const int n = S * E * BLK;
-    for (int idx = threadIdx.x; idx < n; idx += blockDim.x) tabl[(idx / BLK) * BLKL + idx % BLK] = tabg[idx];
-  }
-  __shared__ int lds_k[STEP_K ? kMaxElements : 1];
-  if (STEP_K)
-    for (int e = threadIdx.x; e < E; e += blockDim.x) lds_k[e] = P.kcount[e];
-  __syncthreads();
-
   const int lane = lane_id();
-  const int wv = threadIdx.x / kWave;
   const int64_t N = n_centres(bt), cb = centre_base(bt);
   const int64_t n_items = chunk_off[N] * ng;
   const int NP = (S + NS - 1) / NS;
@@ -531,7 +527,7 @@ __global__ __launch_bounds__(256, pass_slots(MODE, LMAX) == 1 ? 3 : 2) void k_ov
             double v[NH];
 #pragma unroll
             for (int m = 0; m < NH; ++m) v[m] = acc[u].value(m);
-            wave_reduce_store<NH>(v, dst_item + (size_t)__builtin_amdgcn_readlane(so_lane, t) * NH, lds_red[wv]);
+            wave_reduce_store<NH>(v, dst_item + (size_t)__builtin_amdgcn_readlane(so_lane, t) * NH, red);
           }
           acc[u].zero();
         };
@@ -539,6 +535,42 @@ __global__ __launch_bounds__(256, pass_slots(MODE, LMAX) == 1 ? 3 : 2) void k_ov
       }
     }
   }
+}
+
+template <int LMAX, int KB, int MODE, bool LDS, bool SCREEN, bool OCC, bool TAB = false, bool STEP_K = false>
+__global__ __launch_bounds__(256, pass_slots(MODE, LMAX) == 1 ? 3 : 2) void k_overlap(PlanDev P, BatchDev bt, NbrDev nb, const double4 *rw4,
+                                                    const int32_t *astruct, double *partial,
+                                                    const int64_t *chunk_off, int kc, int ng,
+                                                    int nbatch, unsigned long long *counter, const void *tab_global) {
+  using TR = typename std::conditional<MODE == ACC_F64, double, float>::type;  // radial arithmetic
+  constexpr int NH = n_moments(MODE, LMAX), NS = pass_slots(MODE, LMAX);
+  constexpr int BLK = KB * kCoefStride, BLKL = BLK + 16 / (int)sizeof(TR);
+  extern __shared__ __align__(16) double lds_dyn[];
+  __shared__ __align__(16) double lds_red[4][red_doubles(NH)];
+  const int S = P.S, E = P.E;
+  const TR *__restrict__ tabg = (const TR *)tab_global;
+  TR *tabl = (TR *)lds_dyn;
+  if (LDS) {
+    const int n = S * E * BLK;
+    for (int idx = threadIdx.x; idx < n; idx += blockDim.x) tabl[(idx / BLK) * BLKL + idx % BLK] = tabg[idx];
+  }
+  __shared__ int lds_k[STEP_K ? kMaxElements : 1];
+  if (STEP_K)
+    for (int e = threadIdx.x; e < E; e += blockDim.x) lds_k[e] = P.kcount[e];
+  __syncthreads();
+  const int *counts = lds_k;
+  double *red = lds_red[threadIdx.x / kWave];
+  // A lane outside a slot's prefix adds zero times its harmonics to that slot,
+  // which is zero unless they overflow: where a position has diverged since the
+  // lists were built, every slot walks alone, without such lanes.  (A test in
+  // every step instead, of the distance or of the same word: 512 structures 0.94
+  // -> 0.98 ms.)
+  if (NS > 1 && __builtin_amdgcn_readfirstlane((int)counter[1]) != 0)
+    overlap_items<LMAX, KB, MODE, LDS, SCREEN, OCC, TAB, STEP_K, 1, TR>(P, bt, nb, rw4, astruct, partial, chunk_off, kc,
+                                                                     ng, nbatch, counter, tabg, tabl, counts, red);
+  else
+    overlap_items<LMAX, KB, MODE, LDS, SCREEN, OCC, TAB, STEP_K, NS, TR>(P, bt, nb, rw4, astruct, partial, chunk_off, kc,
+                                                                      ng, nbatch, counter, tabg, tabl, counts, red);
 }
 
 // One wavefront per centre: sum chunk partials in order, map moments to
@@ -552,8 +584,9 @@ __global__ __launch_bounds__(256, pass_slots(MODE, LMAX) == 1 ? 3 : 2) void k_ov
 template <int LMAX, bool F64OUT, bool MONO>
 __global__ __launch_bounds__(256) void k_finish(PlanDev P, int64_t N, const double *partial,
                                                 const int64_t *chunk_off, const int32_t *order, void *features,
-                                                double *components) {
+                                                double *components, unsigned long long *counter) {
   extern __shared__ double lds_f[];
+  if (blockIdx.x == 0 && threadIdx.x == 0) counter[1] = 0ull;
   // moment -> component maps of all orders and the multinomial weights,
   // staged in LDS once per workgroup (read with lane-varying indices)
   constexpr int NT = MONO ? kTmat : kHmat;
@@ -834,13 +867,15 @@ void launch_overlap(const gmp_plan *p, const BatchDev &bt, const NbrDev &nb, dou
 }
 
 void launch_finish(const gmp_plan *p, int64_t N, const double *partial, const int64_t *chunk_off,
-                   const int32_t *order, void *features, double *components, hipStream_t s) {
+                   const int32_t *order, void *features, double *components, unsigned long long *counter,
+                   hipStream_t s) {
   if (N == 0) return;
   const int mode = acc_mode(p, components != nullptr), NM = n_moments(mode, p->dev.lmax);
   size_t smem = sizeof(double) * 4 * (size_t)(p->dev.S * NM + p->dev.ncomp_total) +
                 sizeof(int32_t) * (size_t)(p->dev.ncomp_total + p->dev.nf);  // + the decode tables
   int64_t blocks = (N + 3) / 4;
-  using FinishFn = void (*)(PlanDev, int64_t, const double *, const int64_t *, const int32_t *, void *, double *);
+  using FinishFn = void (*)(PlanDev, int64_t, const double *, const int64_t *, const int32_t *, void *, double *,
+                            unsigned long long *);
   static const FinishFn fns[3][kMaxL + 1] = {
       {k_finish<0, true, false>, k_finish<1, true, false>, k_finish<2, true, false>, k_finish<3, true, false>,
        k_finish<4, true, false>},
@@ -850,7 +885,7 @@ void launch_finish(const gmp_plan *p, int64_t N, const double *partial, const in
        k_finish<4, false, true>}};
   const int lm = p->dev.lmax < 0 ? 0 : (p->dev.lmax > kMaxL ? kMaxL : p->dev.lmax);
   GMP_LAUNCH("norm", fns[mode][lm], dim3((unsigned)blocks), dim3(256), smem, s, p->dev, N,
-             partial, chunk_off, order, features, components);
+             partial, chunk_off, order, features, components, counter);
 }
 
 }  // namespace gmp

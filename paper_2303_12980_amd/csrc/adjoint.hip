@@ -732,7 +732,6 @@ using PairsFn = void (*)(PlanDev, BatchDev, NbrDev, const double4 *, const int32
 // differ (FP64: a step's loops end with its own largest count)
 template <int L, int KB, bool F64, bool LDS, bool SCREEN> PairsFn pair_kernel(bool uneven) {
   if constexpr (!F64) return k_bwd_pairs<L, KB, LDS, SCREEN>;
-  else if constexpr (!LDS || SCREEN) return k_bwd_pairs64<L, KB, LDS, SCREEN, true>;
   else return uneven ? k_bwd_pairs64<L, KB, LDS, SCREEN, true> : k_bwd_pairs64<L, KB, LDS, SCREEN, false>;
 }
 template <int L, bool F64, bool LDS, bool SCREEN> PairsFn pick_kb(int kb, bool uneven) {

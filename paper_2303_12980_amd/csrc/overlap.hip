@@ -689,10 +689,10 @@ using OverlapFn = void (*)(PlanDev, BatchDev, NbrDev, const double4 *, const int
 // SCREEN: per-primitive screening; OCC: the neighbours' occupancies scale the
 // terms (without occupancies they are 1, so the variants that are not on the
 // common path always multiply); STEP_K: a step's primitive loops end with the
-// largest count among its own elements, where an exponential is dear (FP64) or a
-// row is tested before it is used (SCREEN).  With one count for all elements the
-// plan's is as good, and the test alone costs (l <= 2, FP64, 1500 atoms: 0.14 ->
-// 0.16 ms).
+// largest count among its own elements, where an exponential is dear (FP64) and
+// the counts differ.  With one count for all elements the plan's is as good, and
+// the test alone costs (l <= 2, 1500 atoms: 0.14 -> 0.16 ms); the screened kernels
+// test every row anyway.
 template <int L, int MODE, bool LDS, bool SCREEN, bool OCC, bool STEP_K> OverlapFn pick_k(int kb) {
   if (kb <= 4) return k_overlap<L, 4, MODE, LDS, SCREEN, OCC, false, STEP_K>;
   if (kb <= 8) return k_overlap<L, 8, MODE, LDS, SCREEN, OCC, false, STEP_K>;
@@ -709,12 +709,12 @@ template <int MODE, bool LDS, bool SCREEN, bool OCC, bool STEP_K> OverlapFn pick
 }
 template <int MODE> OverlapFn pick_overlap(const PlanDev &P, bool lds, bool occ) {
   const int lmax = P.lmax, kb = P.kb;
-  constexpr bool F64 = MODE == ACC_F64;
   if (P.screen)
-    return lds ? pick_l<MODE, true, true, true, true>(lmax, kb) : pick_l<MODE, false, true, true, true>(lmax, kb);
-  if (!lds) return pick_l<MODE, false, false, true, F64>(lmax, kb);
-  if constexpr (F64)
-    if (P.kmin < P.kmax) return pick_l<MODE, true, false, true, true>(lmax, kb);
+    return lds ? pick_l<MODE, true, true, true, false>(lmax, kb) : pick_l<MODE, false, true, true, false>(lmax, kb);
+  if constexpr (MODE == ACC_F64)
+    if (P.kmin < P.kmax)
+      return lds ? pick_l<MODE, true, false, true, true>(lmax, kb) : pick_l<MODE, false, false, true, true>(lmax, kb);
+  if (!lds) return pick_l<MODE, false, false, true, false>(lmax, kb);
   if constexpr (MODE == ACC_TERMS) return pick_l<MODE, true, false, true, false>(lmax, kb);
   else return occ ? pick_l<MODE, true, false, true, false>(lmax, kb) : pick_l<MODE, true, false, false, false>(lmax, kb);
 }

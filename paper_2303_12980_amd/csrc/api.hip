@@ -116,7 +116,7 @@ WsLayout carve(const gmp_plan *p, int n_structs, int64_t N, int64_t M, int64_t c
   L.sz = c.take<double>(N);
   L.sid = c.take<int32_t>(N);
   L.ssp = c.take<int32_t>(N);
-  L.cnt = c.take<int32_t>((size_t)NC * p->dev.E * p->dev.S * p->dev.sub);
+  L.cnt = c.take<int32_t>((size_t)(M > 0 ? M : N) * p->dev.E * p->dev.S * p->dev.sub);  // the centres' alone
   L.ptotal = c.take<int64_t>(NC);
   L.bucket_max = c.take<int32_t>(NC);
   L.long_q = c.take<int32_t>(NC);

@@ -57,7 +57,7 @@ __device__ inline double exp_scaled(double a, double q) { return exp(a * q); }
 // one structure), its structure, and its wrapped position as an AoS double4
 // (one 32-byte gather per neighbour).  The first thread also clears the
 // work-item counter.  The word after the counter tells the overlap kernel of a
-// position that has diverged since the lists were built (kFar).  The neighbour
+// position, occupancy or lattice that has diverged since the lists were built.  The neighbour
 // build clears it, and the norm kernel behind the overlap; a stale one costs time
 // only.
 // Indices g < n_total get their structure and packed position; centres
@@ -68,9 +68,18 @@ __device__ inline int64_t list_chunks(const NbrDev &nb, int kc, int64_t k) {
   // build, reported in the status word): no work items, zero moments
   return end > nb.capacity ? 0 : (kc > 0 && cnt > kc ? (cnt + kc - 1) / kc : 1);
 }
-constexpr double kFar = 1e12;  // monomials of degree 3 do not overflow in FP32 below twice that
-__device__ inline bool far(const double4 &r) {
-  return !(__builtin_fabs(r.x) < kFar && __builtin_fabs(r.y) < kFar && __builtin_fabs(r.z) < kFar);
+// Positions, occupancies and lattice vectors (times up to 126 cells) below these
+// keep every monomial of degree 3 times the occupancy far from overflow in FP32.
+constexpr double kFar = 1e10, kFarOcc = 1e6, kFarCell = 1e7;
+__device__ inline bool diverged(const BatchDev &bt, const double4 &r, int st) {
+  bool ok = __builtin_fabs(r.x) < kFar && __builtin_fabs(r.y) < kFar && __builtin_fabs(r.z) < kFar &&
+            __builtin_fabs(r.w) < kFarOcc;
+  if (bt.pbc[st] & 7) {
+    const double *a = bt.cell + 9 * (int64_t)st;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) ok = ok && __builtin_fabs(a[k]) < kFarCell;
+  }
+  return !ok;
 }
 __device__ inline void prep_index(const BatchDev &bt, const NbrDev &nb, double4 *rw4, int32_t *astruct,
                                   unsigned long long *counter, int64_t i) {
@@ -79,7 +88,7 @@ __device__ inline void prep_index(const BatchDev &bt, const NbrDev &nb, double4 
   astruct[i] = st;
   const double4 r = wrapped_position(bt, nb, i, st);
   rw4[i] = r;
-  if (far(r)) atomicOr(counter + 1, 1ull);
+  if (diverged(bt, r, st)) atomicOr(counter + 1, 1ull);
 }
 __global__ void k_overlap_prep(BatchDev bt, NbrDev nb, int kc, int64_t *nch, double4 *rw4, int32_t *astruct,
                                unsigned long long *counter) {
